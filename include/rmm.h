@@ -591,7 +591,7 @@ rmm_status_t rmm_attention_weights_kmajor_rowstats(const void *S, int64_t batch,
  * energies of rmm_attention_weights_kmajor) and v(u) = b*Hkv + h/(H/Hkv).
  * With causal != 0 the caller states that Pt[u][t][i] = 0 for t > i + (Lk -
  * Lq) (true of rmm_attention_weights_kmajor's causal output); the products
- * of those zeros are then skipped, whole 256-query tiles at a time.
+ * of those zeros are then skipped, whole tiles of queries at a time.
  *
  * Pt : bf16 [batch][H][Lk][ldpt], ldpt >= Lq.   V : bf16 [batch][Hkv][Lk][D].
  * O  : bf16 [batch][H][Lq][D], written.

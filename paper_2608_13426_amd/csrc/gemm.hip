@@ -332,170 +332,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void gemm_gather_bf16_big_kernel(
         }
 }
 
-// ------------------------------------------- bf16, K-major activations
-// Xt[j][m] holds X[m][j] (written by the scoring pass), so a retained index
-// is one contiguous row of Xt, just as it is one contiguous row of W.  Both
-// operands are gathered as 16-byte row vectors: each thread loads an R x 8
-// block (R retained rows, 8 consecutive m or n), transposes it in registers
-// and writes 8 LDS rows of R consecutive k -- the swizzled layout of the
-// large-tile kernel above.  Square tiles of BT = 256 (four waves of 128x128)
-// or 128 (four waves of 64x64); 64 retained indices per k-tile.
-template <int BT, int NW>
-__global__ __launch_bounds__(NW * 64, NW / 4) void gemm_kmajor_bf16_kernel(
-    const uint16_t *__restrict__ Xt, const uint16_t *__restrict__ W,
-    const int32_t *__restrict__ idx, uint16_t *__restrict__ Y, int M, int N, int K, int k,
-    int64_t ldxt, int64_t ldw, int64_t ldy, int64_t xt_bytes, int64_t w_bytes, int tiles_m,
-    int tiles_n) {
-    using big::at;
-    constexpr int BK = big::BK, NT = NW * 64;
-    constexpr int G = BT / 8;             // 8-wide column groups per tile row
-    constexpr int R = BK * G / NT;        // retained rows per thread block
-    constexpr int WN = NW / 2;            // waves: 2 along M, NW/2 along N
-    constexpr int TWM = BT / 2, TWN = BT / WN;
-    constexpr int FM = TWM / 32, FN = TWN / 32;
-    static_assert(R == 4 || R == 8, "thread block");
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2 * 2 * BT * BK];
-
-    const int T = tiles_m * tiles_n;
-    const int bid = blockIdx.x;
-    const int lin = (T % 8 == 0) ? (bid % 8) * (T / 8) + bid / 8 : bid;
-    const int gsz = big::GROUP_M * tiles_n;
-    const int first_m = (lin / gsz) * big::GROUP_M;
-    const int gm = min(big::GROUP_M, tiles_m - first_m);
-    const int m0 = (first_m + (lin % gsz) % gm) * BT;
-    const int n0 = ((lin % gsz) / gm) * BT;
-    const int64_t unit = blockIdx.y;
-    Xt += unit * static_cast<int64_t>(K) * ldxt;
-    Y += unit * static_cast<int64_t>(M) * ldy;
-    idx += unit * k;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c = tid % G, tq = tid / G;   // columns 8c.., retained rows R*tq..
-
-    // Rows past k read out of range (zero); columns past M or N read
-    // neighbouring data that only reaches outputs never stored.
-    constexpr uint32_t kOut = 0x80000000u;
-    const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t *>(Xt), 0, static_cast<uint32_t>(xt_bytes), 0x00020000);
-    const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t *>(W), 0, static_cast<uint32_t>(w_bytes), 0x00020000);
-    const __amdgpu_buffer_rsrc_t ir = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int32_t *>(idx), 0, static_cast<uint32_t>(k) * 4u, 0x00020000);
-    const uint32_t arow = static_cast<uint32_t>(ldxt) * 2u, brow = static_cast<uint32_t>(ldw) * 2u;
-    const uint32_t acol = static_cast<uint32_t>(m0 + 8 * c) * 2u;
-    const uint32_t bcol = static_cast<uint32_t>(n0 + 8 * c) * 2u;
-
-    uint32_t raw[R], ao[R], bo[R];
-    uint4 av[R], bv[R];
-    auto fetch_idx = [&](int t0) {
-#pragma unroll
-        for (int i = 0; i < R; ++i)
-            raw[i] = __builtin_amdgcn_raw_buffer_load_b32(ir, static_cast<uint32_t>(t0 + R * tq + i) * 4u, 0, 0);
-    };
-    auto make_offsets = [&](int t0) {
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const bool in = t0 + R * tq + i < k;
-            ao[i] = in ? raw[i] * arow + acol : kOut;
-            bo[i] = in ? raw[i] * brow + bcol : kOut;
-        }
-    };
-    auto gather = [&]() {
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const auto a = __builtin_amdgcn_raw_buffer_load_b128(ar, ao[i], 0, 0);
-            av[i] = make_uint4(a[0], a[1], a[2], a[3]);
-        }
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const auto b = __builtin_amdgcn_raw_buffer_load_b128(br, bo[i], 0, 0);
-            bv[i] = make_uint4(b[0], b[1], b[2], b[3]);
-        }
-    };
-    // R x 8 block -> 8 LDS rows (8c + jj) of R consecutive k
-    auto put = [&](uint16_t *dst, const uint4 *v) {
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            uint32_t d[R / 2];
-#pragma unroll
-            for (int q = 0; q < R / 2; ++q) {
-                const uint32_t a = reinterpret_cast<const uint32_t *>(&v[2 * q])[jj >> 1];
-                const uint32_t b = reinterpret_cast<const uint32_t *>(&v[2 * q + 1])[jj >> 1];
-                d[q] = (jj & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
-            }
-            if constexpr (R == 8)
-                *reinterpret_cast<uint4 *>(&dst[at(8 * c + jj, tq)]) = make_uint4(d[0], d[1], d[2], d[3]);
-            else
-                *reinterpret_cast<uint2 *>(&dst[at(8 * c + jj, tq >> 1) + 4 * (tq & 1)]) = make_uint2(d[0], d[1]);
-        }
-    };
-
-    f32x16_t acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    const int wm = wave / WN, wn = wave % WN;
-    const int lr = lane & 31, lh = lane >> 5;
-    const int nT = (k + BK - 1) / BK;
-    // buffer b: A at lds + b*BT*BK, B at lds + (2 + b)*BT*BK
-    fetch_idx(0);
-    make_offsets(0);
-    gather();
-    if (nT > 1) fetch_idx(BK);
-    put(lds, av);
-    put(lds + 2 * BT * BK, bv);
-    if (nT > 1) make_offsets(BK);
-    __syncthreads();
-    for (int t = 0; t < nT; ++t) {
-        const int cur = t & 1;
-        const uint16_t *as = lds + cur * BT * BK;
-        const uint16_t *bs = lds + (2 + cur) * BT * BK;
-        if (t + 2 < nT) fetch_idx((t + 2) * BK);
-        if (t + 1 < nT) gather();
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            const int chunk = 2 * ks + lh;
-            bf16x8_t a[FM], b[FN];
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-                a[i] = *reinterpret_cast<const bf16x8_t *>(&as[at(wm * TWM + i * 32 + lr, chunk)]);
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-                b[j] = *reinterpret_cast<const bf16x8_t *>(&bs[at(wn * TWN + j * 32 + lr, chunk)]);
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        if (t + 1 < nT) {
-            put(lds + (cur ^ 1) * BT * BK, av);
-            put(lds + (2 + (cur ^ 1)) * BT * BK, bv);
-        }
-        if (t + 2 < nT) make_offsets((t + 2) * BK);
-        __syncthreads();
-    }
-
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-            const int n = n0 + wn * TWN + j * 32 + lr;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = m0 + wm * TWM + i * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
-                if (m < M && n < N) Y[static_cast<int64_t>(m) * ldy + n] = f32_to_bf16(acc[i][j][v]);
-            }
-        }
-}
-
 // ---------------------- bf16, K-major activations, DMA + transposing reads
-// Same operands as above (rows I(t) of Xt and of W), but nothing passes
-// through registers on the way in: each wave issues 16-byte buffer loads
+// Xt[j][m] holds X[m][j] (written by the scoring pass), so a retained index
+// is one contiguous row of Xt, just as it is one contiguous row of W.  Nothing
+// passes through registers on the way in: each wave issues 16-byte buffer loads
 // that land directly in LDS (a wave fills 1 KiB = two 512-byte staged rows
 // of one operand), and the MFMA fragments are read back with the gfx950
 // transposing LDS read, which hands each lane four consecutive k of one m
@@ -1068,58 +908,64 @@ hipError_t launch_gemm_bf16(const uint16_t *X, const uint16_t *W, const int32_t 
     return hipGetLastError();
 }
 
-constexpr int kKmajorWaves = 8;
 constexpr int kTrWaves = 8, kTrRows = 32, kTrStages = 3;
 
 namespace {
 
+// Which tile: 64 x 64, 128 x 128 or 256 x 256.  Up to 256 of the smallest
+// every CU has at most one, and the smallest tile's K loop is the shortest
+// (37 x 4096 -> 6144, 96 tiles: 11.7 us against 16.4 with 128 x 128).  Beyond, the tile
+// rounds decide, in the times of a round at equal k (2048 x 4096 -> 4096 at
+// k = 2048, us): 49 for up to 256 of the largest tiles, 40 for 512 of the
+// 128 x 128 tiles (two per CU) and 21 for a last round of up to 256 of them.
+enum class KmajorTile { k64, k128, k256 };
+KmajorTile kmajor_tile(int64_t B, int64_t M, int64_t N) {
+    auto count = [&](int64_t t) { return ((M + t - 1) / t) * ((N + t - 1) / t) * B; };
+    if (count(64) <= 256) return KmajorTile::k64;
+    const int64_t c128 = count(128), rest = c128 % 512;
+    const int64_t t128 = c128 / 512 * 40 + (rest == 0 ? 0 : rest <= 256 ? 21 : 40);
+    const int64_t t256 = (count(256) + 255) / 256 * 49;
+    return t128 < t256 ? KmajorTile::k128 : KmajorTile::k256;
+}
+
 // The K-major GEMM over B units; units u read W + (u / w_ugroup) * w_ustride.
-// Grouped weights and K-loop trimming exist only in the large-tile kernel,
-// which then serves small problems too; hipErrorNotSupported (nothing
-// launched) when they are asked for with Y rows too long for its addressing.
+// Grouped weights and K-loop trimming with Y rows of 2^23 elements or more
+// stay refused (hipErrorNotSupported, nothing launched).
 hipError_t kmajor_dispatch(const uint16_t *Xt, const uint16_t *W, const int32_t *idx, int64_t B,
                            int64_t M, int64_t N, int64_t K, int64_t k, int64_t ldxt, int64_t ldw,
                            uint16_t *Y, int64_t ldy, int64_t w_ustride, int w_ugroup,
                            int trim, int64_t trim_off, hipStream_t stream) {
     const int64_t xt_bytes = K * ldxt * 2, w_bytes = K * ldw * 2;
-    const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const bool grouped = (w_ustride != 0 && w_ugroup < B) || trim;
-    // Y rows of one 256-row tile are addressed with 32-bit byte offsets
-    if ((t256 * B >= 128 || grouped) && ldy < (int64_t(1) << 23)) {
-        const int vec_y = (reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 8 == 0) ? 2
-                          : (reinterpret_cast<uintptr_t>(Y) % 8 == 0 && ldy % 4 == 0) ? 1 : 0;
-        const int tm = static_cast<int>((M + 255) / 256);
-        if (N <= 128) {
-            // 256 x 128 tiles: no half-empty tile, two workgroups per CU
-            hipLaunchKernelGGL((gemm_kmajor_tr_kernel<4, kTrRows, kTrStages, 0, 128, 2>),
-                               dim3(tm, static_cast<unsigned>(B)), dim3(4 * 64), 0, stream,
-                               Xt, W, idx, Y, static_cast<int>(M), static_cast<int>(N),
-                               static_cast<int>(k), ldxt, ldw, ldy, xt_bytes, w_bytes, tm, 1, vec_y,
-                               nullptr, w_ustride, w_ugroup, trim, trim_off);
-            return hipGetLastError();
-        }
-        const int tn = static_cast<int>((N + 255) / 256);
-        hipLaunchKernelGGL((gemm_kmajor_tr_kernel<kTrWaves, kTrRows, kTrStages>),
-                           dim3(tm * tn, static_cast<unsigned>(B)), dim3(kTrWaves * 64), 0, stream,
+    // the 256 x 256 kernel addresses one tile's Y rows with 32-bit byte offsets
+    const bool big_ok = ldy < (int64_t(1) << 23);
+    if (grouped && !big_ok) return hipErrorNotSupported;
+    const KmajorTile tile = kmajor_tile(B, M, N);
+    const int tm = static_cast<int>((M + 255) / 256), tn = static_cast<int>((N + 255) / 256);
+    // Value products (N = head dim) take no half-empty 256-wide tile: 256 x 128
+    // from more than two rounds of 128 x 128 tiles on (32 heads x 8192 tokens,
+    // 4096 kept: 424 us against 463; half of that: 132 against 130), unless the
+    // K loops are trimmed, when tiles half as tall stop earlier and balance
+    // better (the same, causal: 250 us against 345).
+    const bool tall = N <= 128 && !trim && (M + 127) / 128 * B > 1024;
+    if (!big_ok || (N <= 128 && !tall) || (N > 128 && tile != KmajorTile::k256))
+        return launch_gemm_kmajor_mid_bf16(tile != KmajorTile::k64, Xt, W, idx, B, M, N, K, k, ldxt, ldw, Y,
+                                           ldy, w_ustride, w_ugroup, trim, trim_off, stream);
+    const int vec_y = (reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 8 == 0) ? 2
+                      : (reinterpret_cast<uintptr_t>(Y) % 8 == 0 && ldy % 4 == 0) ? 1 : 0;
+    if (tall) {
+        hipLaunchKernelGGL((gemm_kmajor_tr_kernel<4, kTrRows, kTrStages, 0, 128, 2>),
+                           dim3(tm, static_cast<unsigned>(B)), dim3(4 * 64), 0, stream,
                            Xt, W, idx, Y, static_cast<int>(M), static_cast<int>(N),
-                           static_cast<int>(k), ldxt, ldw, ldy, xt_bytes, w_bytes, tm, tn, vec_y,
+                           static_cast<int>(k), ldxt, ldw, ldy, xt_bytes, w_bytes, tm, 1, vec_y,
                            nullptr, w_ustride, w_ugroup, trim, trim_off);
         return hipGetLastError();
     }
-    if (grouped) return hipErrorNotSupported;
-    if (t256 * B >= 128) {
-        const int tm = static_cast<int>((M + 255) / 256), tn = static_cast<int>((N + 255) / 256);
-        hipLaunchKernelGGL((gemm_kmajor_bf16_kernel<256, kKmajorWaves>),
-                           dim3(tm * tn, static_cast<unsigned>(B)), dim3(kKmajorWaves * 64), 0, stream, Xt, W, idx, Y, static_cast<int>(M),
-                           static_cast<int>(N), static_cast<int>(K), static_cast<int>(k), ldxt,
-                           ldw, ldy, xt_bytes, w_bytes, tm, tn);
-    } else {
-        const int tm = static_cast<int>((M + 127) / 128), tn = static_cast<int>((N + 127) / 128);
-        hipLaunchKernelGGL((gemm_kmajor_bf16_kernel<128, 4>),
-                           dim3(tm * tn, static_cast<unsigned>(B)), dim3(256), 0, stream, Xt, W, idx, Y, static_cast<int>(M),
-                           static_cast<int>(N), static_cast<int>(K), static_cast<int>(k), ldxt,
-                           ldw, ldy, xt_bytes, w_bytes, tm, tn);
-    }
+    hipLaunchKernelGGL((gemm_kmajor_tr_kernel<kTrWaves, kTrRows, kTrStages>),
+                       dim3(tm * tn, static_cast<unsigned>(B)), dim3(kTrWaves * 64), 0, stream,
+                       Xt, W, idx, Y, static_cast<int>(M), static_cast<int>(N),
+                       static_cast<int>(k), ldxt, ldw, ldy, xt_bytes, w_bytes, tm, tn, vec_y,
+                       nullptr, w_ustride, w_ugroup, trim, trim_off);
     return hipGetLastError();
 }
 

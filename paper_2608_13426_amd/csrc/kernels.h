@@ -82,6 +82,11 @@ hipError_t launch_gemm_kmajor_grouped_bf16(const uint16_t *Xt, const uint16_t *W
                                           int64_t ldxt, int64_t ldw, uint16_t *Y, int64_t ldy,
                                           int64_t w_ustride, int w_ugroup, int trim, int64_t trim_off,
                                           hipStream_t stream);
+// the K-major product in 128 x 128 (wide) or 64 x 64 tiles: any ldy
+hipError_t launch_gemm_kmajor_mid_bf16(bool wide, const uint16_t *Xt, const uint16_t *W, const int32_t *idx,
+                                       int64_t B, int64_t M, int64_t N, int64_t K, int64_t k, int64_t ldxt,
+                                       int64_t ldw, uint16_t *Y, int64_t ldy, int64_t w_ustride, int w_ugroup,
+                                       int trim, int64_t trim_off, hipStream_t stream);
 // the transposing scoring pass over attention scores: Pt = the K-major
 // softmax weights exp(s - rmax[m]) * rinv[m] (zero where causal drops j > m +
 // coff), and their column energies

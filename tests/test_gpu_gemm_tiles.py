@@ -1,0 +1,72 @@
+"""The K-major gathered GEMM's tile choices against the oracle at their edges:
+partial tiles in m and n, list tails of a stage and of the list segment held
+in LDS, unaligned and very long Y rows, several units."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_13426_amd as rmm
+import workloads as wl
+from tests.gpu_util import gpu, require_gpu, to_device, from_device, check_product
+
+pytestmark = gpu
+
+
+@pytest.mark.parametrize("B,M,K,N,k,pad", [
+    (1, 1, 64, 1, 1, 0),            # 64 x 64 tiles: one row, one column, one index
+    (2, 65, 200, 130, 67, 6),       # partial tiles both ways, 8-byte Y rows
+    (1, 63, 136, 200, 64, 5),       # odd Y rows: element stores
+    (1, 40, 3700, 72, 3584, 0),     # the list is exactly one LDS segment
+    (3, 17, 3700, 72, 3585, 0),     # ... and one index more
+    (1, 1100, 160, 1040, 97, 0),    # 128 x 128 tiles: staged and partial columns
+    (1, 1025, 160, 1023, 160, 4),   # ... odd Y rows
+    (2, 700, 3800, 1152, 3700, 4),  # ... two units, two segments, 8-byte Y rows
+    (1, 3000, 72, 3072, 40, 0),     # 256 x 256 tiles (144 of them)
+    (1, 130, 72, 128, 33, 1 << 23), # Y rows too long for 32-bit offsets
+])
+def test_kmajor_tiles(B, M, K, N, k, pad):
+    dev = require_gpu()
+    xs = wl.random_case(300 + M, (B, M, K), "bf16", n_outlier=2)
+    ws = wl.random_case(400 + N, (K, (N + 7) // 8 * 8), "bf16", std=0.02)
+    ldxt = (M + 7) // 8 * 8
+    xt = np.full((B, K, ldxt), 0x7fc0, np.uint16)          # NaN past M: must reach nothing
+    xt[:, :, :M] = xs.transpose(0, 2, 1)
+    rng = np.random.default_rng(M + N)
+    idx = np.sort(np.stack([rng.choice(K, k, replace=False) for _ in range(B)]), axis=1).astype(np.int32)
+    Wd = to_device(ws, "bf16", dev)[:, :N]
+    Y = torch.full((B, M, N + pad), 7.0, dtype=torch.bfloat16, device=dev)
+    rmm.rmm_reduced_gemm_kmajor(to_device(xt, "bf16", dev)[:, :, :M], Wd, torch.from_numpy(idx).to(dev), Y[:, :, :N])
+    W = wl.decode(ws, "bf16").astype(np.float64)[:, :N]
+    got = from_device(Y[:, :, :N])
+    for b in range(B):
+        X = wl.decode(xs, "bf16")[b].astype(np.float64)
+        A = X[:, idx[b]]
+        check_product(got[b], A @ W[idx[b]], np.abs(A) @ np.abs(W[idx[b]]), k, "bf16")
+    tail = Y[:, :, N:N + 64]
+    assert bool((tail == 7.0).all())                       # nothing past N written
+
+
+@pytest.mark.parametrize("H,Hkv,Lq,Lk,kt", [(2, 1, 1, 40, 33), (4, 2, 129, 129, 60), (2, 2, 300, 420, 200),
+                                            (2, 1, 200, 130, 90)])
+def test_pv_kmajor_causal_trim(H, Hkv, Lq, Lk, kt):
+    """The trimmed K loop: a query tile stops at its last visible token, also
+    where Lq != Lk (queries with no visible token get exact zeros)."""
+    dev = require_gpu()
+    D, ld = 128, (Lq + 7) // 8 * 8
+    i, t = np.arange(Lq)[None, :], np.arange(Lk)[:, None]
+    p = np.abs(wl.decode(wl.random_case(7, (H, Lk, Lq), "bf16"), "bf16")).astype(np.float32)
+    p[:, (t > i + (Lk - Lq))] = 0.0
+    pt = np.zeros((1, H, Lk, ld), np.uint16)
+    pt[0, :, :, :Lq] = wl.f32_to_bf16_bits(p)
+    vs = wl.random_case(8, (1, Hkv, Lk, D), "bf16")
+    rng = np.random.default_rng(Lq)
+    idx = np.sort(np.stack([rng.choice(Lk, kt, replace=False) for _ in range(H)]), axis=1).astype(np.int32)
+    O = torch.full((1, H, Lq, D), 7.0, dtype=torch.bfloat16, device=dev)
+    rmm.rmm_reduced_pv_kmajor(to_device(pt, "bf16", dev)[..., :Lq], to_device(vs, "bf16", dev),
+                              torch.from_numpy(idx).to(dev), O, causal=True)
+    got = from_device(O)[0]
+    V = wl.decode(vs, "bf16").astype(np.float64)[0]
+    P = wl.decode(pt, "bf16").astype(np.float64)[0, :, :, :Lq]
+    for h in range(H):
+        A, Vh = P[h][idx[h]].T, V[h // (H // Hkv)][idx[h]]
+        check_product(got[h], A @ Vh, np.abs(A) @ np.abs(Vh), kt, "bf16")
