@@ -4,15 +4,23 @@
 // One workgroup per selection unit.  Each float64 energy is mapped to a
 // 64-bit key whose unsigned order is the order of the values (NaN above
 // +inf, -0 == +0), so the whole selection is integer work: an MSB-first
-// radix select with 8-bit digits finds the k-th largest key, using LDS
-// histograms with integer atomics (order-independent counts).  It starts
-// below the leading bits every key shares and stops as soon as the bucket
-// holding the k-th key is taken whole.  Keys tied with
-// the k-th key are taken lowest index first, and the kept indices are
-// compacted in ascending order with two workgroup prefix scans.  Each thread
-// owns a contiguous chunk of keys, kept in registers when it fits.  For a
-// unit of one token (a decode step) the keys come straight from the token's
-// activations: 16 (bf16) or 31 (fp32) key bits, so at most two passes.
+// radix select with 8-bit digits narrows the keys down to the bucket holding
+// the k-th largest, using LDS histograms with integer atomics
+// (order-independent counts).  It starts below the leading bits every key
+// shares and stops as soon as that bucket is taken whole or holds at most
+// kRankMax keys; those are then ranked directly (a wave per key: ballots over
+// the others).  Keys tied with the k-th key are taken lowest index first, and
+// the kept indices are compacted in ascending order with one workgroup prefix
+// scan.  Each thread owns a contiguous chunk of keys, kept in registers when it
+// fits.  Units of up to 256 keys (attention heads) skip the radix passes: every
+// thread ranks its own key against all of them.  For a unit of one token (a
+// decode step) the keys come straight from the token's activations: 16 (bf16)
+// or 31 (fp32) key bits, so at most two passes.
+//
+// What bounds it is the chain of dependent LDS passes and barriers of one
+// workgroup.
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -27,32 +35,83 @@ __device__ __forceinline__ uint64_t order_key(double d) {
     return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
 
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x, int lane) {
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, kWave);
-        if (lane >= o) x += y;
-    }
+// Inclusive prefix sum over the wave: shifts within rows of 16 lanes, then
+// the last lane of a row into the next one(s) (data-parallel moves, no LDS).
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    auto step = [](uint32_t v, auto ctrl, auto rows) {
+        return v + static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+                       0, static_cast<int>(v), decltype(ctrl)::value, decltype(rows)::value, 0xF, false));
+    };
+    using all = std::integral_constant<int, 0xF>;
+    x = step(x, std::integral_constant<int, 0x111>{}, all{});
+    x = step(x, std::integral_constant<int, 0x112>{}, all{});
+    x = step(x, std::integral_constant<int, 0x114>{}, all{});
+    x = step(x, std::integral_constant<int, 0x118>{}, all{});
+    x = step(x, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
+    x = step(x, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+#endif
     return x;
 }
 
-// Exclusive prefix sum of v over the workgroup in thread order.
+// Exclusive prefix sum of v over the workgroup in thread order (one barrier;
+// `buf`, one word per wave, may be reused only after another).
 template <int NT>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *buf) {
     constexpr int NW = NT / kWave;
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const uint32_t incl = wave_inclusive_scan(v, lane);
+    const int lane = threadIdx.x & (kWave - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t incl = wave_inclusive_scan(v);
     if (lane == kWave - 1) buf[w] = incl;
     __syncthreads();
-    if (w == 0) {
-        const uint32_t x = lane < NW ? buf[lane] : 0u;
-        const uint32_t xi = wave_inclusive_scan(x, lane);
-        if (lane < NW) buf[lane] = xi - x;
+    const uint32_t x = wave_inclusive_scan(lane < NW ? buf[lane] : 0u);
+    const uint32_t before = w == 0 ? 0u : static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), w > 0 ? w - 1 : 0));
+    return before + incl - v;
+}
+
+// Sum of the wave-uniform v over the waves before this one (one barrier).
+template <int NT>
+__device__ __forceinline__ uint32_t waves_before(uint32_t v, uint32_t *buf) {
+    const int lane = threadIdx.x & (kWave - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (lane == 0) buf[w] = v;
+    __syncthreads();
+    uint32_t r = 0;
+#pragma unroll
+    for (int q = 0; q < NT / kWave; ++q) r += q < w ? buf[q] : 0u;
+    return r;
+}
+
+// The 256-bin histogram in HR copies (lane % HR counts into one of them, HS
+// words apart so that one digit's copies sit in different banks): threads
+// 0..255 add up bin 255 - tid, clear its copies for the next pass and find
+// the bin where the descending running count reaches `need`.  Called by the
+// whole workgroup after the counting; out[0..2] = digit, keys above it, its
+// size, valid after the barrier this ends with.
+constexpr int HR = 16, HS = 257;
+__device__ __forceinline__ void pick_digit(uint32_t *hcopy, uint32_t need, uint32_t *wtot, uint32_t *out) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    uint32_t h = 0, incl = 0;
+    __syncthreads();
+    if (tid < 256) {
+#pragma unroll
+        for (int r = 0; r < HR; ++r) {
+            h += hcopy[r * HS + 255 - tid];
+            hcopy[r * HS + 255 - tid] = 0;
+        }
+        incl = wave_inclusive_scan(h);
+        if (lane == kWave - 1) wtot[w] = incl;
     }
     __syncthreads();
-    const uint32_t r = buf[w] + incl - v;
+    if (tid < 256) {
+        uint32_t run = incl - h;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) run += q < w ? wtot[q] : 0u;
+        if (run < need && need <= run + h) {
+            out[0] = 255 - tid;
+            out[1] = run;
+            out[2] = h;
+        }
+    }
     __syncthreads();
-    return r;
 }
 
 // Where the keys come from: a unit's float64 energies, or (a unit of one
@@ -76,29 +135,72 @@ __device__ __forceinline__ uint64_t load_key(const void *row, int64_t j) {
     }
 }
 
+// Units of K <= NT / 4 keys: the quad of lanes t ranks key t against all of
+// them (each lane a quarter; ties to the lower index) and keeps it if fewer
+// than k come before it.  128 heads x 128 keys: 3.6 us against 7.0 for
+// the radix passes.
+template <int NT, int SRC>
+__global__ __launch_bounds__(NT) void select_rank_kernel(const void *__restrict__ src, int64_t ld, int K,
+                                                         int k, int32_t *__restrict__ idx) {
+    constexpr int KP = NT / 4;
+    __shared__ __attribute__((aligned(16))) uint64_t keys[KP];
+    __shared__ uint32_t wcnt[NT / kWave];
+    constexpr int esize = SRC == kEnergy ? 8 : SRC == kTokenBf16 ? 2 : 4;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    const int t = tid >> 2, part = tid & 3;
+    const void *e = static_cast<const char *>(src) + static_cast<int64_t>(blockIdx.x) * ld * esize;
+    int32_t *out = idx + static_cast<int64_t>(blockIdx.x) * k;
+    if (tid < KP) keys[tid] = tid < K ? load_key<SRC>(e, tid) : 0ull;
+    __syncthreads();
+    const uint64_t u = keys[t];
+    int before = 0;
+#pragma unroll 8
+    for (int j = part; j < KP; j += 4) {         // keys past K are 0 and come after every real one
+        const uint64_t o = keys[j];
+        before += o > u || (o == u && j < t);
+    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    before += __builtin_amdgcn_update_dpp(0, before, 0xB1, 0xF, 0xF, false);   // lane ^ 1
+    before += __builtin_amdgcn_update_dpp(0, before, 0x4E, 0xF, 0xF, false);   // lane ^ 2
+#endif
+    const bool keep = part == 0 && t < K && before < k;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+    if (lane == 0) wcnt[w] = static_cast<uint32_t>(__builtin_popcountll(m));
+    __syncthreads();
+    uint32_t pos = static_cast<uint32_t>(__builtin_popcountll(m & ((1ull << lane) - 1)));
+#pragma unroll
+    for (int q = 0; q < NT / kWave; ++q) pos += q < w ? wcnt[q] : 0u;
+    if (keep) out[pos] = t;
+}
+
 // NT threads; C keys per thread held in registers (REG) or re-read from
-// memory (REG == false, chunk size `cpt` at run time).  Unit u's keys start
-// at element u * ld of `src`.
+// memory (REG == false, `cpt` per thread at run time).  A wave owns a
+// contiguous run of the keys, its lanes every 64th of it (whole-line loads
+// and stores; positions come from ballots).  Unit u's keys start at element
+// u * ld of `src`.  Measured (random energies with 1 % outliers, k = K / 2):
+// 10.8 -> 7.2 us at K = 4096 and 24.9 -> 16.4 at K = 14336, against radix
+// passes down to the last digit over keys owned in runs per thread.
+constexpr int kRankMax = 128;      // ranked at once: two per lane (256: 9.6 us instead of 6.4 at K = 1024)
 template <int NT, int C, bool REG, int SRC>
 __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src, int64_t ld,
                                                     int64_t K, int64_t k, int cpt,
                                                     int32_t *__restrict__ idx) {
-    // lanes count into HR copies of the histogram (lane % HR), HR + 1 words
-    // apart so that one digit's copies sit in different banks: the keys of a
-    // unit often share a digit, and one copy would take most of a wave's
-    // increments on one word
-    constexpr int HR = 16, HS = 257;
+    constexpr int NW = NT / kWave;
     __shared__ uint32_t hcopy[HR * HS];
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t scan_buf[NT / kWave];
-    __shared__ uint32_t s_digit, s_above, s_count;
+    __shared__ uint32_t scan_buf[NW], wtot[4], s_pick[3], s_n;
+    __shared__ uint32_t s_min[NW], s_max[NW];
+    __shared__ uint64_t cand_key[kRankMax], s_thr;
+    __shared__ int32_t cand_idx[kRankMax], s_tie;
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     constexpr int esize = SRC == kEnergy ? 8 : SRC == kTokenBf16 ? 2 : 4;
     const void *e = static_cast<const char *>(src) + static_cast<int64_t>(blockIdx.x) * ld * esize;
     int32_t *out = idx + static_cast<int64_t>(blockIdx.x) * k;
     const int chunk = REG ? C : cpt;
-    const int64_t c0 = static_cast<int64_t>(tid) * chunk;
+    // key c of this lane is index c0 + 64 * c
+    const int64_t c0 = static_cast<int64_t>(wave) * chunk * kWave + lane;
+    const uint64_t below = (1ull << lane) - 1;
 
     if (k == K) {                       // everything is kept
         for (int64_t j = tid; j < K; j += NT) out[j] = static_cast<int32_t>(j);
@@ -109,59 +211,57 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
     if constexpr (REG) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const int64_t j = c0 + c;
+            const int64_t j = c0 + kWave * c;
             keys[c] = j < K ? load_key<SRC>(e, j) : 0ull;
         }
     }
+    for (int i = tid; i < HR * HS; i += NT) hcopy[i] = 0;
+    if (tid == 0) s_n = 0;
     auto key_at = [&](int c) -> uint64_t {
         if constexpr (REG) return keys[c];
-        else return load_key<SRC>(e, c0 + c);
+        else return load_key<SRC>(e, c0 + static_cast<int64_t>(kWave) * c);
     };
-    const int n_own = static_cast<int>(max<int64_t>(0, min<int64_t>(chunk, K - c0)));
+    const int n_own = static_cast<int>(max<int64_t>(0, min<int64_t>(chunk, (K - c0 + kWave - 1) / kWave)));
 
     // The leading bits shared by every key need no pass (energies of one
-    // unit usually share sign and most of the exponent): take the
-    // workgroup's smallest and largest key and start below their common
-    // prefix, so the first pass already spreads the keys over its buckets.
-    uint64_t kmin = ~0ull, kmax = 0;
+    // unit usually share sign and most of the exponent): take the workgroup's
+    // smallest and largest high word (a token's keys have only a low word)
+    // and start below their common prefix, so the first pass already spreads
+    // the keys over its buckets.
+    constexpr int SH = SRC == kEnergy ? 32 : 0;
+    uint32_t kmin = ~0u, kmax = 0;
     for (int c = 0; c < n_own; ++c) {
-        const uint64_t u = key_at(c);
-        kmin = u < kmin ? u : kmin;
-        kmax = u > kmax ? u : kmax;
+        const uint32_t u = static_cast<uint32_t>(key_at(c) >> SH);
+        kmin = min(kmin, u);
+        kmax = max(kmax, u);
     }
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
-        const uint64_t a = __shfl_xor(kmin, o, kWave), b = __shfl_xor(kmax, o, kWave);
-        kmin = a < kmin ? a : kmin;
-        kmax = b > kmax ? b : kmax;
+        kmin = min(kmin, static_cast<uint32_t>(__shfl_xor(static_cast<int>(kmin), o, kWave)));
+        kmax = max(kmax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(kmax), o, kWave)));
     }
-    __shared__ uint64_t s_min[NT / kWave], s_max[NT / kWave];
-    if ((tid & (kWave - 1)) == 0) { s_min[tid / kWave] = kmin; s_max[tid / kWave] = kmax; }
+    if (lane == 0) { s_min[wave] = kmin; s_max[wave] = kmax; }
     __syncthreads();
     kmin = s_min[0];
     kmax = s_max[0];
 #pragma unroll
-    for (int w = 1; w < NT / kWave; ++w) {
-        kmin = s_min[w] < kmin ? s_min[w] : kmin;
-        kmax = s_max[w] > kmax ? s_max[w] : kmax;
+    for (int w = 1; w < NW; ++w) {
+        kmin = min(kmin, s_min[w]);
+        kmax = max(kmax, s_max[w]);
     }
-    uint64_t prefix, mask;
-    int top;                                        // highest bit not yet fixed
-    if (kmin == kmax) {
-        prefix = kmin; mask = ~0ull; top = -1;       // all keys equal: ties by index
-    } else {
-        top = 63 - __builtin_clzll(kmin ^ kmax);
-        mask = top == 63 ? 0ull : (~0ull << (top + 1));
-        prefix = kmax & mask;
-    }
+    // top: the highest bit not yet fixed
+    int top = kmin == kmax ? SH - 1 : SH + 31 - __builtin_clz(kmin ^ kmax);
+    uint64_t mask = top == 63 ? 0ull : (~0ull << (top + 1));
+    uint64_t prefix = (static_cast<uint64_t>(kmax) << SH) & mask;
     uint32_t need = static_cast<uint32_t>(k);
     uint32_t *hmine = hcopy + (tid % HR) * HS;
+    // keys above `prefix` (under `mask`) are kept, and keys equal to it up to index `tie`
+    int64_t tie = -1;
+    bool decided = false;
     while (top >= 0) {
         // digit: bits top .. shift (up to 8 of them)
         const int shift = max(0, top - 7);
         const uint64_t dmask = (1ull << (top - shift + 1)) - 1;
-        for (int i = tid; i < HR * HS; i += NT) hcopy[i] = 0;
-        __syncthreads();
         if constexpr (REG) {
 #pragma unroll
             for (int c = 0; c < C; ++c)
@@ -173,62 +273,95 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
                 if ((u & mask) == prefix) atomicAdd(&hmine[(u >> shift) & dmask], 1u);
             }
         }
-        __syncthreads();
-        for (int i = tid; i < 256; i += NT) {
-            uint32_t t = 0;
-#pragma unroll
-            for (int r = 0; r < HR; ++r) t += hcopy[r * HS + i];
-            hist[i] = t;
-        }
-        __syncthreads();
-        if (tid < kWave) {
-            // lane L holds digits 255-4L .. 252-4L (descending value order)
-            uint32_t h[4], sum = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) { h[q] = hist[255 - 4 * tid - q]; sum += h[q]; }
-            const uint32_t incl = wave_inclusive_scan(sum, tid);
-            uint32_t run = incl - sum;
-            if (run < need && need <= incl) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (run + h[q] >= need) {
-                        s_digit = 255 - 4 * tid - q;
-                        s_above = run;
-                        s_count = h[q];
-                        break;
-                    }
-                    run += h[q];
-                }
-            }
-        }
-        __syncthreads();
-        need -= s_above;
-        prefix |= static_cast<uint64_t>(s_digit) << shift;
+        pick_digit(hcopy, need, wtot, s_pick);
+        need -= s_pick[1];
+        prefix |= static_cast<uint64_t>(s_pick[0]) << shift;
         mask |= dmask << shift;
         top = shift - 1;
-        if (s_count == need) break;      // the whole bucket is kept
-    }
-
-    // candidates share the prefix; keep the first `need` of them by index
-    uint32_t n_cand = 0;
-    for (int c = 0; c < n_own; ++c) n_cand += ((key_at(c) & mask) == prefix);
-    uint32_t cand = block_exclusive_scan<NT>(n_cand, scan_buf);
-    uint32_t n_sel = 0;
-    {
-        uint32_t cc = cand;
-        for (int c = 0; c < n_own; ++c) {
-            const uint64_t p = key_at(c) & mask;
-            if (p > prefix) ++n_sel;
-            else if (p == prefix) { n_sel += (cc < need); ++cc; }
+        const uint32_t n = s_pick[2];
+        if (n == need) { tie = K; decided = true; break; }      // the whole bucket is kept
+        if (n <= kRankMax) {
+            // rank the bucket's keys: the one with need - 1 before it is the k-th
+            for (int c = 0; c < n_own; ++c) {
+                const uint64_t u = key_at(c);
+                if ((u & mask) == prefix) {
+                    const uint32_t p = atomicAdd(&s_n, 1u);
+                    cand_key[p] = u;
+                    cand_idx[p] = static_cast<int32_t>(c0 + kWave * c);
+                }
+            }
+            __syncthreads();
+            uint64_t ck[kRankMax / kWave];
+            int32_t ci[kRankMax / kWave];
+#pragma unroll
+            for (int q = 0; q < kRankMax / kWave; ++q) {
+                const uint32_t j = static_cast<uint32_t>(lane + kWave * q);
+                ck[q] = j < n ? cand_key[j] : 0ull;
+                ci[q] = j < n ? cand_idx[j] : 0x7fffffff;     // past the end: before no candidate
+            }
+            for (uint32_t i = wave; i < n; i += NW) {
+                const uint64_t ki = cand_key[i];
+                const int32_t ii = cand_idx[i];
+                uint32_t before = 0;
+#pragma unroll
+                for (int q = 0; q < kRankMax / kWave; ++q)
+                    before += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(
+                        ck[q] > ki || (ck[q] == ki && ci[q] < ii))));
+                if (before == need - 1 && lane == 0) { s_thr = ki; s_tie = ii; }
+            }
+            __syncthreads();
+            prefix = s_thr;
+            mask = ~0ull;
+            tie = s_tie;
+            decided = true;
+            break;
         }
     }
-    uint32_t pos = block_exclusive_scan<NT>(n_sel, scan_buf);
-    for (int c = 0; c < n_own; ++c) {
-        const uint64_t p = key_at(c) & mask;
-        bool keep = p > prefix;
-        if (p == prefix) { keep = cand < need; ++cand; }
-        if (keep) out[pos++] = static_cast<int32_t>(c0 + c);
+    if (!decided) {
+        // more than kRankMax equal keys at the threshold: keep the first
+        // `need` of them by index
+        auto tied = [&](int c) { return c < n_own && (key_at(c) & mask) == prefix; };
+        uint32_t n_cand = 0;
+        for (int c = 0; c < chunk; ++c)
+            n_cand += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(tied(c))));
+        uint32_t cand = waves_before<NT>(n_cand, scan_buf);
+        for (int c = 0; c < chunk; ++c) {
+            const bool t = tied(c);
+            const uint64_t m = __builtin_amdgcn_ballot_w64(t);
+            if (t && cand + static_cast<uint32_t>(__builtin_popcountll(m & below)) == need - 1)
+                s_tie = static_cast<int32_t>(c0 + static_cast<int64_t>(kWave) * c);
+            cand += static_cast<uint32_t>(__builtin_popcountll(m));
+        }
+        __syncthreads();
+        tie = s_tie;
     }
+
+    auto kept = [&](int c) {
+        if (c >= n_own) return false;
+        const uint64_t p = key_at(c) & mask;
+        return p > prefix || (p == prefix && c0 + static_cast<int64_t>(kWave) * c <= tie);
+    };
+    auto each = [&](auto &&f) {
+        if constexpr (REG) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) f(c);
+        } else {
+            for (int c = 0; c < chunk; ++c) f(c);
+        }
+    };
+    uint32_t n_sel = 0;
+    each([&](int c) {
+        n_sel += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(kept(c))));
+    });
+    uint32_t pos = waves_before<NT>(n_sel, scan_buf);
+    each([&](int c) {
+        const bool keep = kept(c);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+        if (keep)
+            out[pos + static_cast<uint32_t>(__builtin_popcountll(m & below))] =
+                static_cast<int32_t>(c0 + static_cast<int64_t>(kWave) * c);
+        pos += static_cast<uint32_t>(__builtin_popcountll(m));
+    });
 }
 
 // One bf16 token per workgroup (a decode step), K <= 32 * 1024 (at most
@@ -246,14 +379,9 @@ __device__ __forceinline__ void select_token16(const uint16_t *__restrict__ x, i
     static_assert(C % 8 == 0 && C <= 32 && NT >= 256 && NT <= 1024, "chunk");
     // The keys of a token bunch up in a few digits (one per binary exponent),
     // so one histogram would take most of a wave's 64 increments on one
-    // word.  Lanes count into HR copies (lane % HR), HR + 1 words apart so
-    // that one digit's copies sit in different banks, and the copies are
-    // summed before the scan.
-    constexpr int HR = 16, HS = 257;
+    // word: hence its copies.
     __shared__ uint32_t hcopy[HR * HS];
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t scan_buf[NT / kWave];
-    __shared__ int s_thr, s_need;
+    __shared__ uint32_t scan_buf[NT / kWave], wtot[4], s_pick[3];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     if (k == K) {                       // everything is kept
         for (int j = tid; j < K; j += NT) out[j] = j;
@@ -273,14 +401,14 @@ __device__ __forceinline__ void select_token16(const uint16_t *__restrict__ x, i
             key[8 * q + e] = c0 + 8 * q + e < K ? (h > 0x7f80u ? 0x7fc0u : h) : 0x8000u;
         }
     }
+    for (int j = tid; j < HR * HS; j += NT) hcopy[j] = 0;
     // pass 1 over bits 14..7, pass 2 over bits 6..0 of the keys in the chosen bucket
     int need = k, thr = -1, take_ties = 0;
     int prefix = -1;                    // pass-1 digit, once chosen
     uint32_t *hmine = hcopy + (lane % HR) * HS;
+    __syncthreads();
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-        for (int j = tid; j < HR * HS; j += NT) hcopy[j] = 0;
-        __syncthreads();
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const uint32_t u = key[c];
@@ -288,38 +416,9 @@ __device__ __forceinline__ void select_token16(const uint16_t *__restrict__ x, i
             if (pass == 0) atomicAdd(&hmine[u >> 7], 1u);
             else if (static_cast<int>(u >> 7) == prefix) atomicAdd(&hmine[u & 0x7fu], 1u);
         }
-        __syncthreads();
-        if (tid < 256) {
-            uint32_t t = 0;
-#pragma unroll
-            for (int r = 0; r < HR; ++r) t += hcopy[r * HS + tid];
-            hist[tid] = t;
-        }
-        __syncthreads();
-        if (tid < kWave) {
-            // lane L holds digits 255-4L .. 252-4L (descending value order)
-            uint32_t h[4], sum = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) { h[q] = hist[255 - 4 * lane - q]; sum += h[q]; }
-            const uint32_t incl = wave_inclusive_scan(sum, lane);
-            uint32_t run = incl - sum;
-            const uint32_t nd = static_cast<uint32_t>(need);
-            if (run < nd && nd <= incl) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (run + h[q] >= nd) {
-                        s_thr = 255 - 4 * lane - q;
-                        s_need = static_cast<int>(nd - run);   // keys of this bucket to keep
-                        hist[0] = h[q];                        // its size (read after the barrier)
-                        break;
-                    }
-                    run += h[q];
-                }
-            }
-        }
-        __syncthreads();
-        const int d = s_thr, nb = s_need, size = static_cast<int>(hist[0]);
-        __syncthreads();                // hist is rewritten by the next pass
+        pick_digit(hcopy, static_cast<uint32_t>(need), wtot, s_pick);
+        const int d = static_cast<int>(s_pick[0]), nb = need - static_cast<int>(s_pick[1]);
+        const int size = static_cast<int>(s_pick[2]);          // keys of this bucket, nb of them to keep
         if (pass == 0) {
             if (size == nb) { thr = (d << 7) - 1; take_ties = 0; break; }   // the whole bucket
             prefix = d;
@@ -390,10 +489,15 @@ hipError_t launch(const void *src, int64_t ld, int64_t B, int64_t K, int64_t k, 
 template <int SRC>
 hipError_t launch_src(const void *src, int64_t ld, int64_t B, int64_t K, int64_t k, int32_t *idx,
                       hipStream_t stream) {
-    if (K <= 256) return launch<256, 1, true, SRC>(src, ld, B, K, k, 1, idx, stream);
-    if (K <= 512) return launch<256, 2, true, SRC>(src, ld, B, K, k, 2, idx, stream);
-    if (K <= 1024) return launch<256, 4, true, SRC>(src, ld, B, K, k, 4, idx, stream);
-    if (K <= 2048) return launch<256, 8, true, SRC>(src, ld, B, K, k, 8, idx, stream);
+    if (K <= 256) {
+        auto rank = K <= 128 ? select_rank_kernel<512, SRC> : select_rank_kernel<1024, SRC>;
+        hipLaunchKernelGGL(rank, dim3(static_cast<unsigned>(B)), dim3(K <= 128 ? 512 : 1024), 0, stream, src, ld,
+                           static_cast<int>(K), static_cast<int>(k), idx);
+        return hipGetLastError();
+    }
+    if (K <= 512) return launch<512, 1, true, SRC>(src, ld, B, K, k, 1, idx, stream);
+    if (K <= 1024) return launch<512, 2, true, SRC>(src, ld, B, K, k, 2, idx, stream);
+    if (K <= 2048) return launch<512, 4, true, SRC>(src, ld, B, K, k, 4, idx, stream);
     if (K <= 4096) return launch<1024, 4, true, SRC>(src, ld, B, K, k, 4, idx, stream);
     if (K <= 8192) return launch<1024, 8, true, SRC>(src, ld, B, K, k, 8, idx, stream);
     if (K <= 16384) return launch<1024, 16, true, SRC>(src, ld, B, K, k, 16, idx, stream);

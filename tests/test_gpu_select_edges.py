@@ -1,0 +1,50 @@
+"""Selection at the edges of its paths (direct ranking of short units, radix
+passes that end in a ranked bucket, more ties at the threshold than are
+ranked) against the oracle's rule: energy descending, ties to the lower index,
+NaN above +inf."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_13426_amd as rmm
+from tests.gpu_util import gpu, require_gpu
+
+pytestmark = gpu
+
+
+def _top(e, k):
+    v = np.where(np.isnan(e), np.inf, e)
+    order = np.lexsort((np.arange(e.size), -v, ~np.isnan(e)))
+    return np.sort(order[:k])
+
+
+def _values(kind, rng, B, K):
+    if kind == "ties":                      # a handful of distinct values
+        e = rng.integers(0, 3, (B, K)).astype(np.float64)
+    elif kind == "zeros":                   # mostly exact zeros, both signs
+        e = np.where(rng.random((B, K)) < 0.1, rng.random((B, K)), 0.0) * rng.choice([-0.0, 1.0], (B, K))
+    elif kind == "close":                   # equal leading 40 bits, some equal altogether
+        e = 1.0 + rng.integers(0, 200, (B, K)) * 2.0 ** -50
+    elif kind == "special":
+        e = rng.standard_normal((B, K)) ** 2
+        e[rng.random((B, K)) < 0.05] = np.inf
+        e[rng.random((B, K)) < 0.05] = np.nan
+    else:                                   # a bulk within a few percent, 1 % outliers
+        e = 1.0 + 0.03 * rng.standard_normal((B, K))
+        e[rng.random((B, K)) < 0.01] *= 400.0
+    return e
+
+
+@pytest.mark.parametrize("kind", ["bulk", "ties", "zeros", "close", "special"])
+@pytest.mark.parametrize("B,K", [(3, 1), (2, 127), (33, 128), (2, 129), (4, 256), (2, 257), (1, 512), (2, 513),
+                                 (1, 2049), (2, 4100), (1, 16385), (1, 33000)])
+def test_select_edges(kind, B, K):
+    dev = require_gpu()
+    rng = np.random.default_rng(K)
+    e = _values(kind, rng, B, K)
+    for k in sorted({1, (K + 1) // 2, max(1, K - 1), K}):
+        idx = torch.full((B * k,), -1, dtype=torch.int32, device=dev)
+        rmm.rmm_select(torch.from_numpy(e).to(dev), k, idx)
+        got = idx.cpu().numpy().reshape(B, k)
+        for b in range(B):
+            assert np.array_equal(got[b], _top(e[b], k)), (kind, B, K, k, b)
