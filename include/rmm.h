@@ -344,7 +344,8 @@ rmm_status_t rmm_reduced_qk_rowstats(const void *Q, const void *Kc, const int32_
  * idx : int32 [batch*H*k], each head's list ascending (from rmm_select).
  * workspace : rmm_workspace_size(RMM_OP_ATTENTION, batch*H, Lk, D, k) bytes,
  *       16-byte aligned; receives each query head's retained key dims as
- *       contiguous rows (overwritten by every call).
+ *       contiguous rows or, for few query rows against many keys, partial
+ *       outputs (overwritten by every call).
  * Scores and the softmax are computed in fp32, the weights rounded to bf16
  * for the value product, fp32 accumulation, bf16 output.
  * Errors: INVALID_ARGUMENT as rmm_reduced_qk, or a misaligned workspace;

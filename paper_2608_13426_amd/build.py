@@ -19,7 +19,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "librmm.so")
 
 SOURCES = ("api.hip", "score.hip", "select.hip", "gemm.hip", "gemm_mid.hip", "gemv.hip", "gemv_shared.hip", "qk.hip", "attn.hip",
-           "noalloc.hip", "norm.hip", "weights.hip")
+           "attn_few.hip", "noalloc.hip", "norm.hip", "weights.hip")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -564,6 +564,8 @@ hipError_t launch_attn_bf16(const uint16_t *Q, const uint16_t *Kc, const uint16_
                             const int32_t *idx, int64_t batch, int64_t H, int64_t Hkv,
                             int64_t Lq, int64_t Lk, int64_t k, float scale, bool causal,
                             uint16_t *O, void *workspace, hipStream_t stream) {
+    if (attn_few_ok(batch, H, Hkv, Lq, Lk, k))
+        return launch_attn_few_bf16(Q, Kc, V, idx, batch, H, Hkv, Lq, Lk, k, scale, causal, O, workspace, stream);
     return launch_attn<false>(Q, Kc, V, idx, batch, H, Hkv, Lq, Lk, k, scale, causal, O,
                               static_cast<uint16_t *>(workspace), 0, nullptr, stream);
 }
@@ -573,6 +575,9 @@ hipError_t launch_attn_kmajor_bf16(const uint16_t *Q, const uint16_t *Kc, const 
                                    int64_t Lq, int64_t Lk, int64_t k, float scale, bool causal,
                                    uint16_t *Ot, int64_t ldot, double *energy, uint16_t *Ki,
                                    double *partials, hipStream_t stream) {
+    if (attn_few_ok(batch, H, Hkv, Lq, Lk, k))
+        return launch_attn_few_kmajor_bf16(Q, Kc, V, idx, batch, H, Hkv, Lq, Lk, k, scale, causal, Ot, ldot, energy,
+                                           Ki, stream);
     const hipError_t e = launch_attn<true>(Q, Kc, V, idx, batch, H, Hkv, Lq, Lk, k, scale, causal,
                                            Ot, Ki, ldot, partials, stream);
     if (e != hipSuccess) return e;

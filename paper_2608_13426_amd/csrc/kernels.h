@@ -163,6 +163,17 @@ hipError_t launch_attn_bf16(const uint16_t *Q, const uint16_t *Kc, const uint16_
                             const int32_t *idx, int64_t batch, int64_t H, int64_t Hkv,
                             int64_t Lq, int64_t Lk, int64_t k, float scale, bool causal,
                             uint16_t *O, void *workspace, hipStream_t stream);
+// the same block, and its K-major form, for few query rows per head
+// (attn_few_ok): the keys are split over workgroups, the workspace
+// (attn_workspace_bytes) takes as many splits' partial outputs as fit
+bool attn_few_ok(int64_t batch, int64_t H, int64_t Hkv, int64_t Lq, int64_t Lk, int64_t k);
+hipError_t launch_attn_few_bf16(const uint16_t *Q, const uint16_t *Kc, const uint16_t *V, const int32_t *idx,
+                                int64_t batch, int64_t H, int64_t Hkv, int64_t Lq, int64_t Lk, int64_t k,
+                                float scale, bool causal, uint16_t *O, void *workspace, hipStream_t stream);
+hipError_t launch_attn_few_kmajor_bf16(const uint16_t *Q, const uint16_t *Kc, const uint16_t *V,
+                                       const int32_t *idx, int64_t batch, int64_t H, int64_t Hkv, int64_t Lq,
+                                       int64_t Lk, int64_t k, float scale, bool causal, uint16_t *Ot,
+                                       int64_t ldot, double *energy, void *workspace, hipStream_t stream);
 // the same block writing its output as the K-major input of the following
 // projection, Ot[b][h*D + j][ldot] (Lq % 8 == 0, ldot % 8 == 0, Ot 16-byte
 // aligned), and that input's column energies energy[b][h*D + j]; partials
