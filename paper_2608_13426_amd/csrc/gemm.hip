@@ -12,7 +12,7 @@
 // multiplied.  Index tails (k not a multiple of BK) and M/N tails are zero-
 // filled; no compacted copy of either operand is ever written to memory.
 //
-// fp32 path: the same gather into LDS with a VALU FMA tile (fp32 accumulate).
+// fp32 path: the same gather into LDS, fp32 MFMA tiles.
 #include <type_traits>
 
 #include "device_common.h"
@@ -814,61 +814,133 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_kmajor_tr_kernel(
 }
 
 // ------------------------------------------------------------------ fp32
-template <int BM, int BN, int BK>
+// v_mfma_f32_16x16x4_f32 (fp32 products and sums) on BM x BN tiles, four waves
+// of (BM/2) x (BN/2), BK retained indices per double-buffered LDS tile.  Both
+// operands lie k-contiguous in LDS (rows of BK + 4 floats: 16-byte reads of
+// eight rows fall on distinct banks); lane group g reads k = 4g .. 4g+3 of a
+// 16-index step and MFMA e takes element e of both.  The next tile's values
+// are in registers while this one is multiplied, and its indices one tile
+// further ahead.  X is gathered with lanes along the list (one row's retained
+// columns share lines); W comes as 4 x 4 blocks (four rows, 16 bytes each)
+// transposed in registers.  Tails of the list are zeros; rows past M and
+// columns past N are loaded clamped and never stored.  Bound by the length of
+// the list's dependent tiles at small sizes and by LDS reads at large ones.
+// Against the 64 x 64 VALU tile it replaces (us): 128 x 512 -> 512 at k = 256
+// 46.3 -> 11.2 (launch included; 7.1 alone), 1024^3 at k = 512 131 -> 25, 4096^3
+// at k = 2048 1433 -> 908 (76 of about 150 TFLOP/s); the same error.
+template <int BM, int BN, int BK, bool VECW>
 __global__ __launch_bounds__(256) void gemm_gather_f32_kernel(
     const float *__restrict__ X, const float *__restrict__ W, const int32_t *__restrict__ idx,
-    float *__restrict__ Y, int M, int N, int k, int64_t ldx, int64_t ldw, int64_t ldy) {
-    constexpr int TX = 16, TY = 16;                  // 256 threads
-    constexpr int RM = BM / TY, RN = BN / TX;        // outputs per thread
-    __shared__ float As[BK][BM + 1];
-    __shared__ float Bs[BK][BN + 1];
-    const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
+    float *__restrict__ Y, int M, int N, int k, int64_t ldx, int64_t ldw, int64_t ldy, int vec_y) {
+    constexpr int LS = BK + 4;                       // floats per LDS row
+    constexpr int FM = BM / 32, FN = BN / 32;        // 16 x 16 fragments per wave
+    constexpr int RPP = 256 / BK, XR = BM / RPP;     // X rows per pass and per thread
+    constexpr int NQ = BN / 4, WT = BK / 4 * NQ;     // 4 x 4 blocks of W per tile
+    static_assert(WT <= 256 && BM % RPP == 0 && BK % 16 == 0, "tile split");
+    __shared__ __attribute__((aligned(16))) float As[2][BM * LS], Bs[2][BN * LS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
     const int64_t unit = blockIdx.z;
     X += unit * static_cast<int64_t>(M) * ldx;
     Y += unit * static_cast<int64_t>(M) * ldy;
     idx += unit * k;
 
-    float acc[RM][RN];
+    const int xt = tid % BK, xr0 = tid / BK;         // X role: list position, first row
+    const int wk = 4 * (tid / NQ), wn = 4 * (tid % NQ);   // W role (threads below WT)
+    const bool w_on = WT == 256 || tid < WT;
+    int32_t xj, wj[4];
+    auto fetch_idx = [&](int t0) {
+        xj = t0 + xt < k ? idx[t0 + xt] : -1;
 #pragma unroll
-    for (int i = 0; i < RM; ++i)
+        for (int i = 0; i < 4; ++i) wj[i] = w_on && t0 + wk + i < k ? idx[t0 + wk + i] : -1;
+    };
+    float xv[XR];
+    f32x4_t wv[4];
+    auto gather = [&]() {
 #pragma unroll
-        for (int j = 0; j < RN; ++j) acc[i][j] = 0.f;
+        for (int i = 0; i < XR; ++i) {
+            const int m = min(m0 + xr0 + i * RPP, M - 1);
+            xv[i] = xj >= 0 ? X[static_cast<int64_t>(m) * ldx + xj] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            wv[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (wj[i] < 0) continue;
+            const float *p = W + static_cast<int64_t>(wj[i]) * ldw;
+            const int n = n0 + wn;
+            if (VECW && n + 4 <= N) {
+                wv[i] = *reinterpret_cast<const f32x4_t *>(p + n);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) wv[i][e] = p[min(n + e, N - 1)];
+            }
+        }
+    };
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < XR; ++i) As[buf][(xr0 + i * RPP) * LS + xt] = xv[i];
+        if (w_on) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                *reinterpret_cast<f32x4_t *>(&Bs[buf][(wn + e) * LS + wk]) = f32x4_t{wv[0][e], wv[1][e], wv[2][e], wv[3][e]};
+        }
+    };
 
-    for (int t0 = 0; t0 < k; t0 += BK) {
-        // X tile: lanes along the retained position within one row
-        for (int v = tid; v < BM * BK; v += 256) {
-            const int c = v % BK, r = v / BK;
-            const int t = t0 + c, m = m0 + r;
-            As[c][r] = (t < k && m < M) ? X[static_cast<int64_t>(m) * ldx + idx[t]] : 0.f;
+    f32x4_t acc[FN][FM];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int i = 0; i < FM; ++i) acc[j][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int lr = lane & 15, lg = lane >> 4;
+    const int wm = (wave >> 1) * (BM / 2), wnb = (wave & 1) * (BN / 2);
+    fetch_idx(0);
+    gather();
+    fetch_idx(BK);
+    stash(0);
+    __syncthreads();
+    for (int t0 = 0, buf = 0; t0 < k; t0 += BK, buf ^= 1) {
+        if (t0 + BK < k) {
+            gather();
+            fetch_idx(t0 + 2 * BK);
         }
-        for (int v = tid; v < BK * BN; v += 256) {
-            const int c = v / BN, n = v % BN;
-            const int t = t0 + c;
-            Bs[c][n] = (t < k && n0 + n < N) ? W[static_cast<int64_t>(idx[t]) * ldw + n0 + n] : 0.f;
+#pragma unroll
+        for (int ks = 0; ks < BK; ks += 16) {
+            f32x4_t a[FM], b[FN];
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+                a[i] = *reinterpret_cast<const f32x4_t *>(&As[buf][(wm + 16 * i + lr) * LS + ks + 4 * lg]);
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                b[j] = *reinterpret_cast<const f32x4_t *>(&Bs[buf][(wnb + 16 * j + lr) * LS + ks + 4 * lg]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+                        acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][e], a[i][e], acc[j][i], 0, 0, 0);
         }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < BK; ++c) {
-            float a[RM], b[RN];
-#pragma unroll
-            for (int i = 0; i < RM; ++i) a[i] = As[c][ty + i * TY];
-#pragma unroll
-            for (int j = 0; j < RN; ++j) b[j] = Bs[c][tx + j * TX];
-#pragma unroll
-            for (int i = 0; i < RM; ++i)
-#pragma unroll
-                for (int j = 0; j < RN; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
+        if (t0 + BK < k) stash(buf ^ 1);
         __syncthreads();
     }
+    // acc[j][i][r]: n = n0 + wnb + 16j + 4*(lane/16) + r, m = m0 + wm + 16i + lane%16
 #pragma unroll
-    for (int i = 0; i < RM; ++i)
+    for (int i = 0; i < FM; ++i) {
+        const int m = m0 + wm + 16 * i + lr;
+        if (m >= M) continue;
 #pragma unroll
-        for (int j = 0; j < RN; ++j) {
-            const int m = m0 + ty + i * TY, n = n0 + tx + j * TX;
-            if (m < M && n < N) Y[static_cast<int64_t>(m) * ldy + n] = acc[i][j];
+        for (int j = 0; j < FN; ++j) {
+            const int n = n0 + wnb + 16 * j + 4 * lg;
+            float *p = Y + static_cast<int64_t>(m) * ldy + n;
+            if (vec_y && n + 4 <= N) {
+                *reinterpret_cast<f32x4_t *>(p) = acc[j][i];
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (n + r < N) p[r] = acc[j][i][r];
+            }
         }
+    }
 }
 
 }  // namespace
@@ -1008,12 +1080,21 @@ hipError_t launch_gemm_f32(const float *X, const float *W, const int32_t *idx, i
                            int64_t M, int64_t N, int64_t K, int64_t k, int64_t ldx, int64_t ldw,
                            float *Y, int64_t ldy, hipStream_t stream) {
     (void)K;
-    constexpr int BM = 64, BN = 64, BK = 16;
-    dim3 grid(static_cast<unsigned>((N + BN - 1) / BN), static_cast<unsigned>((M + BM - 1) / BM),
-              static_cast<unsigned>(B));
-    hipLaunchKernelGGL((gemm_gather_f32_kernel<BM, BN, BK>), grid, dim3(256), 0, stream, X, W, idx, Y,
-                       static_cast<int>(M), static_cast<int>(N), static_cast<int>(k), ldx, ldw, ldy);
-    return hipGetLastError();
+    const bool vec = reinterpret_cast<uintptr_t>(W) % 16 == 0 && ldw % 4 == 0;
+    const int vec_y = reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 4 == 0;
+    // 64 x 64 tiles once they give every CU one, 32 x 32 (a quarter of the work
+    // per workgroup) below
+    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64) * B;
+    const int t = t64 >= 256 ? 64 : 32;
+    auto launch = [&](auto kernel) {
+        dim3 grid(static_cast<unsigned>((N + t - 1) / t), static_cast<unsigned>((M + t - 1) / t),
+                  static_cast<unsigned>(B));
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, X, W, idx, Y, static_cast<int>(M),
+                           static_cast<int>(N), static_cast<int>(k), ldx, ldw, ldy, vec_y);
+        return hipGetLastError();
+    };
+    if (t == 64) return vec ? launch(gemm_gather_f32_kernel<64, 64, 32, true>) : launch(gemm_gather_f32_kernel<64, 64, 32, false>);
+    return vec ? launch(gemm_gather_f32_kernel<32, 32, 64, true>) : launch(gemm_gather_f32_kernel<32, 32, 64, false>);
 }
 
 }  // namespace rmm

@@ -70,3 +70,27 @@ def test_pv_kmajor_causal_trim(H, Hkv, Lq, Lk, kt):
     for h in range(H):
         A, Vh = P[h][idx[h]].T, V[h // (H // Hkv)][idx[h]]
         check_product(got[h], A @ Vh, np.abs(A) @ np.abs(Vh), kt, "bf16")
+
+
+@pytest.mark.parametrize("B,M,K,N,k,wpad", [
+    (1, 1, 5, 1, 1, 0),             # 32 x 32 tiles: a single product
+    (2, 33, 200, 61, 65, 3),        # partial tiles, one index past a list tile, rows of W unaligned
+    (1, 40, 130, 64, 128, 4),       # whole list tiles
+    (1, 1025, 96, 1030, 31, 2),     # 64 x 64 tiles: list shorter than a tile, 8-byte rows
+    (3, 600, 100, 640, 97, 0),      # ... several units
+])
+def test_f32_tiles(B, M, K, N, k, wpad):
+    dev = require_gpu()
+    xs = wl.random_case(500 + M, (B, M, K), "f32", n_outlier=2)
+    ws = wl.random_case(600 + N, (K, N + wpad), "f32", std=0.02)
+    rng = np.random.default_rng(M * N)
+    idx = np.sort(np.stack([rng.choice(K, k, replace=False) for _ in range(B)]), axis=1).astype(np.int32)
+    Y = torch.full((B, M, N + 3), 7.0, dtype=torch.float32, device=dev)
+    rmm.rmm_reduced_gemm(to_device(xs, "f32", dev), to_device(ws, "f32", dev)[:, :N], torch.from_numpy(idx).to(dev),
+                         Y[:, :, :N])
+    got = Y.double().cpu().numpy()
+    assert np.all(got[:, :, N:] == 7.0)
+    W = ws.astype(np.float64)[:, :N]
+    for b in range(B):
+        A = xs[b].astype(np.float64)[:, idx[b]]
+        check_product(got[b][:, :N], A @ W[idx[b]], np.abs(A) @ np.abs(W[idx[b]]), k, "f32")
