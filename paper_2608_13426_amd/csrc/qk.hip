@@ -2,12 +2,13 @@
 //   S[h] = scale * Q[h][:, I_h] K[g(h)][:, I_h]^T,  -inf where causally masked,
 // with g(h) = h / (H / Hkv).
 //
-// Both operands are rows gathered along the head dimension (a Q row and a K
-// row are each D contiguous values), so each k-tile is a lane-along-t gather
-// into n-major / m-major LDS tiles that feed v_mfma_f32_32x32x16_bf16
-// directly.  The kernel is bound by writing S (Lq*Lk values per head), which
-// does not shrink with k; tiles lying wholly above the causal diagonal skip
-// the product and only write -inf.
+// A Q row and a K row are each D contiguous values.  The kernels are bound by
+// writing S (Lq*Lk values per head), which does not shrink with k; tiles lying
+// wholly above the causal diagonal skip the product and only write -inf.  Head
+// dims of 64 and 128 take the row-streaming kernel below; other head dims the
+// tile kernel, whose operands are gathered at the retained dims.
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -124,22 +125,26 @@ __global__ __launch_bounds__(WM *WN *kWave) void qk_bf16_kernel(
 }
 
 // ------------------------------------------------------- row-streaming kernel
-// One workgroup per (head, 128-query tile) walks the key tiles (BT keys:
-// 128 with 4 waves, or 256 with 8 waves) of its rows.
-// Q and K rows (D values, 16-byte chunks) are read whole and staged in LDS
-// with an odd row stride of D/2+1 words, so 32 rows read at one column hit
-// 32 distinct banks; the MFMA operands are gathered from the staged rows at
-// the retained dims (a zeroed pad word stands in for padding positions).
-// Q's fragments are gathered once and kept in registers.  The waves split
-// the 128 x BT tile into KW key strips and WQ query strips: with few retained
-// dims (KSMAX k-steps) one strip of 32 keys per wave against all 128
-// queries, so no K fragment is gathered twice; with more, two query strips
-// keep Q's register footprint in bounds.  The product is
-// formed transposed (keys x queries), so each lane holds 4 consecutive keys
-// of one query; tiles are staged through LDS and written as coalesced
-// 16-byte stores, BT*2-byte row pieces (the longer pieces of the 256-key
-// tiles write faster).  Key tiles wholly above the diagonal are streamed
-// as -inf.
+// One workgroup per (head, 128-query tile, share of the key tiles) walks its
+// key tiles (BT keys: 128 with 4 waves, or 256 with 8 waves).  Q and K rows (D
+// values, 16-byte chunks) are read whole and staged in LDS.
+//   Masked (the usual form): the dropped dims are cleared on the way into LDS
+//   and the product runs over all D dims, with 16-byte fragment reads.  The
+//   matrix work is the same for every k and stays behind the stores.
+//   Gathered (GATHER, long rows with few dims): an odd row stride of D/2+1
+//   words, so 32 rows read at one column hit 32 distinct banks; the fragments
+//   are gathered at the retained dims with 2-byte reads (a zeroed pad word
+//   stands in for padding positions).  With few dims kept one strip of 32 keys
+//   per wave against all 128 queries, so no K fragment is gathered twice.
+// Q's fragments are kept in registers.  The waves split the 128 x BT tile into
+// KW key strips and WQ query strips.  The product is formed transposed (keys x
+// queries), so each lane holds 4 consecutive keys of one query; tiles are
+// staged through LDS and written as coalesced 16-byte stores, BT*2-byte row
+// pieces.  Key tiles wholly above the diagonal are streamed as -inf.
+// Bound by writing S.  Measured (us, causal, before -> now; gathered fragments,
+// no key shares and a 2-byte fallback for odd rows before): 32 heads x 1001 keys,
+// k = 103 53.6 -> 18.5; x 1024, k = 64 19.3 -> 15.9; x 4096, k = 64 249 -> 232 (4.6
+// TB/s); x 4095 642 -> 331; 8 sequences x 32 heads, one query x 4001 keys 99 -> 45.
 namespace rowk {
 constexpr int BQ = 128;       // queries per block
 // cache policy of the score stores (sc1).  Streaming (nt) stores measured
@@ -154,34 +159,44 @@ constexpr int kStoreAux = 16;
 // its rows, a running maximum over its 8-key chunks and a sum rescaled when
 // the maximum rises; a row's threads are consecutive lanes, merged at the end
 // in a fixed butterfly.
-template <int D, int KSMAX, int WQ, int NTT, int BTT, bool ST = false>
+// MODE: 0 rows on 16-byte boundaries; 1 any rows (buffer stores need no
+// alignment; the chunk a row ends in goes out element by element); 2 any rows,
+// shifted to lines: row pieces that do not cover whole 128-byte lines write at
+// about 60 % of the rate of those that do, so the pieces start at line
+// boundaries and each row's elements past the last one wait for the next tile.
+template <int D, int WQ, int NTT, int BTT, bool ST = false, int MODE = 0, bool GATHER = false>
 __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ Kc,
     const int32_t *__restrict__ idx, uint16_t *__restrict__ S, int H, int Hkv, int Lq, int Lk,
-    int k, float scale, int causal, float *__restrict__ rmax = nullptr,
+    int k, float scale, int causal, int C, float *__restrict__ rmax = nullptr,
     float *__restrict__ rinv = nullptr) {
     constexpr int BQ = rowk::BQ, BT = BTT, NT = NTT;
-    constexpr int OS = BT + 8;             // staged output row (16-byte aligned)
+    constexpr bool RAG = MODE == 2, ANY = MODE > 0;
+    constexpr int PRE = RAG ? 64 : 0;      // the previous tile's last columns before a staged row
+    constexpr int OS = PRE + BT + 8;       // staged output row (16-byte aligned)
     typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-    constexpr int kStoreAux = rowk::kStoreAux;
-    constexpr int RW = D / 2 + 1;          // words per staged row (odd)
+    constexpr int kStoreAux = RAG ? 0 : rowk::kStoreAux;
+    constexpr int RW = GATHER ? D / 2 + 1 : D / 2;   // words per staged row (odd: 32 rows, 32 banks)
+    constexpr int KSMAX = GATHER ? 4 : D / 16;       // k-steps
     constexpr int CH = D / 8;              // 16-byte chunks per row
     constexpr int PER_T = BT * CH / NT;    // chunks staged per thread
     constexpr int KW = NT / 64 / WQ;       // waves along keys
     constexpr int FI = BT / KW / 32;       // 32-key fragments per wave
     constexpr int FJ = BQ / WQ / 32;       // 32-query fragments per wave
     static_assert(D % 16 == 0 && BT % BQ == 0 && (BT * CH) % NT == 0, "shape");
-    static_assert(KSMAX * 16 <= D && (WQ == 1 || WQ == 2), "shape");
+    static_assert((WQ == 1 || WQ == 2) && NT % CH == 0, "shape");
 
-    __shared__ uint32_t rows_lds[BT * RW];
+    __shared__ __attribute__((aligned(1024))) uint32_t rows_lds[BT * RW];
     __shared__ __attribute__((aligned(16))) uint16_t out_lds[BQ * OS];
-    __shared__ __attribute__((aligned(16))) uint16_t col_off[D + 16];
+    // masked: 0xffff at the retained dims; gathered: their byte offsets in a row
+    __shared__ __attribute__((aligned(16))) uint16_t dims[D + 16];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int bh = blockIdx.y, b = bh / H, h = bh % H, g = h / (H / Hkv);
     // causal: the last query tiles carry the most key tiles, so they are
     // dealt first (longest work first keeps the tail of the grid short)
-    const int qt = causal ? static_cast<int>(gridDim.x) - 1 - static_cast<int>(blockIdx.x) : blockIdx.x;
+    const int qx = static_cast<int>(blockIdx.x) / C, chunk = static_cast<int>(blockIdx.x) % C;
+    const int qt = causal ? static_cast<int>(gridDim.x) / C - 1 - qx : qx;
     const int q0 = qt * BQ;
     const int off = Lk - Lq;
     const int32_t *I = idx + static_cast<int64_t>(bh) * k;
@@ -192,23 +207,30 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
         const int limit = min(q0 + BQ, Lq) - 1 + off;   // largest key any row keeps
         n_compute = limit < 0 ? 0 : min(n_tiles, limit / BT + 1);
     }
-    constexpr int CPR = BT / 8, RPP = NT / CPR;        // 16-byte chunks per row piece, rows per pass
-    const int r16 = tid / CPR, c16 = tid % CPR;         // store role: rows r16 + RPP*i, chunk c16
+    // this block's key tiles: [t_lo, t_hi), the first nc of them with a product
+    const int tpc = (n_tiles + C - 1) / C, t_lo = chunk * tpc, t_hi = min(n_tiles, t_lo + tpc);
+    const int nc = max(0, min(t_hi, n_compute) - t_lo);
+    // Store role: a wave instruction covers RPI row pieces of the tile, CPR
+    // 16-byte chunks each; RAG: of rows equal mod 8 (one 16-byte misalignment)
+    constexpr int CPR = BT / 8, RPI = 64 / CPR, NWV = NT / 64;
+    constexpr int RES = 8 / NWV, SR = BQ / RPI / NWV, IPR = SR / RES;   // residues, instructions (and each) per wave
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int c16 = lane % CPR;
+    auto row_of = [&](int i) {
+        return RAG ? wave_u + NWV * (i / IPR) + 8 * (RPI * (i % IPR) + lane / CPR) : tid / CPR + RPI * NWV * i;
+    };
+    // RAG: elements between the last 128-byte boundary of memory and row r
+    const int s_mis = RAG ? static_cast<int>((reinterpret_cast<uintptr_t>(Sh + static_cast<int64_t>(q0) * Lk) / 2) & 63) : 0;
+    auto mis = [&](int r) { return RAG ? (s_mis + r * Lk) & 63 : 0; };
     // the block's rows of S; rows at or past Lq fall outside the range and are dropped
     const __amdgpu_buffer_rsrc_t sr = __builtin_amdgcn_make_buffer_rsrc(
         Sh + static_cast<int64_t>(q0) * Lk, 0, static_cast<uint32_t>(min(BQ, Lq - q0) * Lk * 2),
         0x00020000);
-    constexpr int SR = BQ / RPP;              // rows per thread in the store role
     float st_m[SR], st_l[SR];                 // their running statistics (ST)
 #pragma unroll
     for (int i = 0; i < SR; ++i) { st_m[i] = -__builtin_inff(); st_l[i] = 0.f; }
 
-    if (n_compute > 0) {
-        const int kp = (k + 15) & ~15;
-        const int KS = kp / 16;
-        for (int t = tid; t < D + 16; t += NT) col_off[t] = static_cast<uint16_t>((t < k ? I[t] : D) * 2);
-        for (int r = tid; r < BT; r += NT) rows_lds[r * RW + D / 2] = 0u;
-
+    if (nc > 0) {
         const __amdgpu_buffer_rsrc_t qr = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t *>(Q + (static_cast<int64_t>(bh) * Lq + q0) * D), 0,
             static_cast<uint32_t>(min(BQ, Lq - q0) * D * 2), 0x00020000);
@@ -224,12 +246,23 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
                 regs[i] = make_uint4(x[0], x[1], x[2], x[3]);
             }
         };
+        // masked: a thread's chunks all lie in one 16-byte column of the rows, so
+        // one mask clears the dropped dims on the way into LDS (bitwise: an
+        // infinite or NaN value there stays without effect); chunk c of row r
+        // sits at c ^ (r % CH)
+        const int KS = GATHER ? (k + 15) / 16 : KSMAX;
+        uint4 km = make_uint4(0, 0, 0, 0);
         auto store_rows = [&]() {
 #pragma unroll
             for (int i = 0; i < PER_T; ++i) {
-                const int v = tid + NT * i;
-                uint32_t *dst = rows_lds + (v / CH) * RW + (v % CH) * 4;
-                dst[0] = regs[i].x; dst[1] = regs[i].y; dst[2] = regs[i].z; dst[3] = regs[i].w;
+                const int v = tid + NT * i, r = v / CH;
+                if constexpr (GATHER) {
+                    uint32_t *dst = rows_lds + r * RW + (v % CH) * 4;
+                    dst[0] = regs[i].x; dst[1] = regs[i].y; dst[2] = regs[i].z; dst[3] = regs[i].w;
+                } else {
+                    *reinterpret_cast<uint4 *>(rows_lds + r * RW + 4 * ((v % CH) ^ (r & (CH - 1)))) =
+                        make_uint4(regs[i].x & km.x, regs[i].y & km.y, regs[i].z & km.z, regs[i].w & km.w);
+                }
             }
         };
         auto key_rsrc = [&](int kt) {
@@ -238,25 +271,41 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
                 const_cast<uint16_t *>(Kh + static_cast<int64_t>(t0) * D), 0,
                 static_cast<uint32_t>(min(BT, Lk - t0) * D * 2), 0x00020000);
         };
-        // 8 retained dims (k-step ks, lane half) of staged row `row`
+        // 8 dims (k-step ks, lane half) of staged row `row`
         auto frag = [&](int row, int ks) -> bf16x8_t {
-            const uint4 co = *reinterpret_cast<const uint4 *>(&col_off[ks * 16 + 8 * (lane >> 5)]);
-            const char *base = reinterpret_cast<const char *>(rows_lds + row * RW);
-            const uint32_t o[4] = {co.x, co.y, co.z, co.w};
-            uint32_t w[4];
+            if constexpr (GATHER) {
+                const uint4 co = *reinterpret_cast<const uint4 *>(&dims[ks * 16 + 8 * (lane >> 5)]);
+                const char *base = reinterpret_cast<const char *>(rows_lds + row * RW);
+                const uint32_t o[4] = {co.x, co.y, co.z, co.w};
+                uint32_t w[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t lo = *reinterpret_cast<const uint16_t *>(base + (o[q] & 0xffffu));
-                const uint32_t hi = *reinterpret_cast<const uint16_t *>(base + (o[q] >> 16));
-                w[q] = lo | (hi << 16);
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t lo = *reinterpret_cast<const uint16_t *>(base + (o[q] & 0xffffu));
+                    const uint32_t hi = *reinterpret_cast<const uint16_t *>(base + (o[q] >> 16));
+                    w[q] = lo | (hi << 16);
+                }
+                return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
+            } else {
+                return *reinterpret_cast<const bf16x8_t *>(
+                    rows_lds + row * RW + 4 * ((2 * ks + (lane >> 5)) ^ (row & (CH - 1))));
             }
-            return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
         };
 
         const int wk = wave / WQ, wq = wave % WQ;   // wave: BT/KW keys x BQ/WQ queries
         const int lr = lane & 31, lh = lane >> 5;
 
+        // the query rows pass through the key rows' space; BT >= BQ
         load_rows(qr);
+        if constexpr (GATHER) {
+            for (int t = tid; t < D + 16; t += NT) dims[t] = static_cast<uint16_t>((t < k ? I[t] : D) * 2);
+            for (int r = tid; r < BT; r += NT) rows_lds[r * RW + D / 2] = 0u;    // what padding positions read
+        } else {
+            if (tid < D / 8) reinterpret_cast<uint4 *>(dims)[tid] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+            if (tid < k) dims[I[tid]] = 0xffffu;
+            __syncthreads();
+            km = reinterpret_cast<const uint4 *>(dims)[tid % CH];
+        }
         store_rows();
         __syncthreads();
         bf16x8_t qf[FJ][KSMAX];
@@ -264,22 +313,28 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
         for (int j = 0; j < FJ; ++j)
 #pragma unroll
             for (int ks = 0; ks < KSMAX; ++ks)
-                if (ks < KS) qf[j][ks] = frag((wq * FJ + j) * 32 + lr, ks);
+                if (!GATHER || ks < KS) qf[j][ks] = frag((wq * FJ + j) * 32 + lr, ks);
         // Each block walks its key tiles starting at a tile of its own and
         // wrapping around, so that at any moment the blocks store to
         // different column ranges of their rows (all starting at column 0
         // measured about 1.5x slower without the causal mask: the row pieces
         // of simultaneous tiles then share too few memory channels).
-        const int rot = (bh * 5 + qt) % n_compute;
-        auto tile_at = [&](int i) { const int t = i + rot; return t >= n_compute ? t - n_compute : t; };
+        const int rot = (bh * 5 + qt) % nc;
+        auto tile_at = [&](int i) { const int t = i + rot; return t_lo + (t >= nc ? t - nc : t); };
         load_rows(key_rsrc(tile_at(0)));
         __syncthreads();
         store_rows();
         __syncthreads();
 
-        for (int it = 0; it < n_compute; ++it) {
+        // RAG: the last 64 columns of a tile, kept for the next tile's first lines
+        constexpr int CC = BQ * 8 / NT;
+        uint4 carry[CC];
+#pragma unroll
+        for (int i = 0; i < CC; ++i) carry[i] = make_uint4(0, 0, 0, 0);
+        const bool row8 = Lk % 8 == 0 && (s_mis & 7) == 0;      // every row 16-byte aligned
+        for (int it = 0; it < nc; ++it) {
             const int kt = tile_at(it);
-            if (it + 1 < n_compute) load_rows(key_rsrc(tile_at(it + 1)));
+            if (it + 1 < nc) load_rows(key_rsrc(tile_at(it + 1)));
             f32x16_t acc[FI][FJ];
 #pragma unroll
             for (int i = 0; i < FI; ++i)
@@ -289,14 +344,13 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
                     for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KSMAX; ++ks) {
-                if (ks < KS) {
+                if (GATHER && ks >= KS) continue;
 #pragma unroll
-                    for (int i = 0; i < FI; ++i) {
-                        const bf16x8_t kf = frag((wk * FI + i) * 32 + lr, ks);
+                for (int i = 0; i < FI; ++i) {
+                    const bf16x8_t kf = frag((wk * FI + i) * 32 + lr, ks);
 #pragma unroll
-                        for (int j = 0; j < FJ; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[j][ks], acc[i][j], 0, 0, 0);
-                    }
+                    for (int j = 0; j < FJ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[j][ks], acc[i][j], 0, 0, 0);
                 }
             }
             // acc[i][j][4*gq + r]: key (wk*FI + i)*32 + 8*gq + 4*lh + r, query (wq*FJ + j)*32 + lr
@@ -320,29 +374,127 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
                             if (lim < 2) w1 = (w1 & 0xffff0000u) | kBf16NegInf;
                             if (lim < 3) w1 = (w1 & 0x0000ffffu) | (static_cast<uint32_t>(kBf16NegInf) << 16);
                         }
-                        *reinterpret_cast<uint2 *>(&out_lds[ql * OS + kl]) = make_uint2(w0, w1);
+                        *reinterpret_cast<uint2 *>(&out_lds[ql * OS + PRE + kl]) = make_uint2(w0, w1);
                     }
                 }
-            lds_barrier();
-            const int col = kt * BT + c16 * 8;
-            uint4 staged[BQ / RPP];
+            if constexpr (RAG) {
 #pragma unroll
-            for (int i = 0; i < BQ / RPP; ++i) {
-                const int r = r16 + RPP * i;
-                // unconditional (a column past Lk goes out of range): a branch
-                // here would make the compiler's wait for the next K rows also
-                // wait for these stores
-                const uint32_t off = col < Lk ? static_cast<uint32_t>((r * Lk + col) * 2) : 0x80000000u;
-                const uint4 v = *reinterpret_cast<const uint4 *>(&out_lds[r * OS + c16 * 8]);
-                __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{v.x, v.y, v.z, v.w}, sr, off, 0, kStoreAux);
-                staged[i] = v;
+                for (int i = 0; i < CC; ++i) {
+                    const int v = tid + NT * i;
+                    *reinterpret_cast<uint4 *>(&out_lds[(v >> 3) * OS + 8 * (v & 7)]) = carry[i];
+                }
+            }
+            lds_barrier();
+            auto lds_chunk = [&](int r, int e) { return *reinterpret_cast<const uint4 *>(&out_lds[r * OS + e]); };
+            auto put1 = [&](uint16_t x, int r, int col, bool on) __attribute__((always_inline)) {
+                __builtin_amdgcn_raw_buffer_store_b16(x, sr, on ? static_cast<uint32_t>((r * Lk + col) * 2) : 0x80000000u, 0, kStoreAux);
+            };
+            const int t0 = kt * BT;
+            uint4 staged[SR];
+            if constexpr (!RAG) {
+#pragma unroll
+                for (int i = 0; i < SR; ++i) {
+                    const int r = row_of(i), col = t0 + 8 * c16;
+                    staged[i] = lds_chunk(r, 8 * c16);
+                    // unconditional (a column past Lk goes out of range): a branch
+                    // here would make the compiler's wait for the next K rows also
+                    // wait for these stores
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{staged[i].x, staged[i].y, staged[i].z, staged[i].w}, sr,
+                        (ANY ? col + 8 <= Lk : col < Lk) ? static_cast<uint32_t>((r * Lk + col) * 2) : 0x80000000u, 0, kStoreAux);
+                }
+                if constexpr (ANY) {
+                    if (t0 + BT > Lk) {                   // the elements after the row's last whole chunk
+#pragma unroll
+                        for (int r0 = 0; r0 < BQ; r0 += NT / 8) {
+                            const int r = r0 + (tid >> 3), cl = ((Lk - t0) & ~7) + (tid & 7);
+                            put1(out_lds[r * OS + cl], r, t0 + cl, t0 + cl < Lk);
+                        }
+                    }
+                }
+            } else {
+                // whole 128-byte lines: columns t0 - m .. t0 + BT - m - 1 of a row m
+                // elements past a line boundary, the first m from the tile before
+                const bool first = it == 0 || kt == t_lo, last = it == nc - 1 || kt == t_lo + nc - 1;
+                auto put = [&](int i0, auto SHv) __attribute__((always_inline)) {
+                    constexpr int SH = decltype(SHv)::value;      // m % 8
+#pragma unroll
+                    for (int ii = 0; ii < IPR; ++ii) {
+                        const int r = row_of(i0 + ii), m = mis(r), e = PRE - (m & ~7) + 8 * c16;
+                        uint4 x = lds_chunk(r, e);
+                        if constexpr (SH > 0) {
+                            // the previous chunk's last SH elements, then this one's first 8 - SH
+                            const uint4 p = lds_chunk(r, e - 8);
+                            const uint32_t d[8] = {p.x, p.y, p.z, p.w, x.x, x.y, x.z, x.w};
+                            constexpr int ds = (8 - SH) >> 1;
+                            uint32_t o[4];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                o[q] = SH & 1 ? __builtin_amdgcn_alignbit(d[ds + q + 1], d[ds + q], 16) : d[ds + q];
+                            x = make_uint4(o[0], o[1], o[2], o[3]);
+                        }
+                        const int col = t0 - m + 8 * c16;
+                        __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{x.x, x.y, x.z, x.w}, sr,
+                            col + 8 <= Lk && !(first && col < t0) ? static_cast<uint32_t>((r * Lk + col) * 2) : 0x80000000u, 0, kStoreAux);
+                    }
+                };
+#pragma unroll
+                for (int u = 0; u < RES; ++u) {
+                    switch (mis(wave_u + NWV * u) & 7) {
+                    case 0: put(u * IPR, std::integral_constant<int, 0>{}); break;
+                    case 1: put(u * IPR, std::integral_constant<int, 1>{}); break;
+                    case 2: put(u * IPR, std::integral_constant<int, 2>{}); break;
+                    case 3: put(u * IPR, std::integral_constant<int, 3>{}); break;
+                    case 4: put(u * IPR, std::integral_constant<int, 4>{}); break;
+                    case 5: put(u * IPR, std::integral_constant<int, 5>{}); break;
+                    case 6: put(u * IPR, std::integral_constant<int, 6>{}); break;
+                    default: put(u * IPR, std::integral_constant<int, 7>{}); break;
+                    }
+                }
+                if (first) {                              // the elements before the first whole chunk
+#pragma unroll
+                    for (int r0 = 0; r0 < BQ; r0 += NT / 8) {
+                        const int r = r0 + (tid >> 3), e = tid & 7, sh = mis(r) & 7;
+                        put1(out_lds[r * OS + PRE + e], r, t0 + e, sh > 0 && e < 8 - sh && t0 + e < Lk);
+                    }
+                }
+                if (t0 + BT > Lk) {                       // the elements after the row's last whole chunk
+#pragma unroll
+                    for (int r0 = 0; r0 < BQ; r0 += NT / 8) {
+                        const int r = r0 + (tid >> 3), m = mis(r);
+                        const int cl = min((Lk - t0 + m) & ~7, BT) - m + (tid & 7);   // column within the tile
+                        put1(out_lds[r * OS + PRE + cl], r, t0 + cl, t0 + cl < Lk && cl < BT - m && !(first && cl < 0));
+                    }
+                }
+                if (last) {
+                    // what the next tile's lines would take: m elements per row
+                    if (row8) {
+#pragma unroll
+                        for (int r0 = 0; r0 < BQ; r0 += NT / 8) {
+                            const int r = r0 + (tid >> 3), m = mis(r), cl = BT - m + 8 * (tid & 7);
+                            const uint4 x = lds_chunk(r, PRE + min(cl, BT - 8));
+                            __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{x.x, x.y, x.z, x.w}, sr,
+                                cl < BT && t0 + cl < Lk ? static_cast<uint32_t>((r * Lk + t0 + cl) * 2) : 0x80000000u, 0, kStoreAux);
+                        }
+                    } else {
+                        for (int r = wave; r < BQ; r += NWV) {
+                            const int cl = BT - mis(r) + lane;
+                            put1(out_lds[r * OS + PRE + min(cl, BT - 1)], r, t0 + cl, cl < BT && t0 + cl < Lk);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < CC; ++i) {
+                    const int v = tid + NT * i;
+                    carry[i] = lds_chunk(v >> 3, PRE + BT - 64 + 8 * (v & 7));
+                }
             }
             if constexpr (ST) {
                 // After the stores are issued, so that this work overlaps their
                 // drain, and without branches, for the same reason as above.
                 // Masked keys hold -inf already; a chunk past Lk is not scores.
 #pragma unroll
-                for (int i = 0; i < BQ / RPP; ++i) {
+                for (int i = 0; i < SR; ++i) {
+                    const int col = t0 + 8 * c16;
                     const uint32_t w[4] = {staged[i].x, staged[i].y, staged[i].z, staged[i].w};
                     float e[8];
                     float cm = -__builtin_inff();
@@ -362,7 +514,7 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
                     st_l[i] = l;
                 }
             }
-            if (it + 1 < n_compute) store_rows();
+            if (it + 1 < nc) store_rows();
             lds_barrier();
         }
     }
@@ -380,7 +532,7 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
                     st_l[i] = a + c;
                 }
             }
-            const int r = r16 + RPP * i;
+            const int r = row_of(i);
             if (c16 == 0 && q0 + r < Lq) {
                 const int64_t row = static_cast<int64_t>(bh) * Lq + q0 + r;
                 const bool empty = !(st_l[i] > 0.f);
@@ -392,12 +544,24 @@ __global__ __launch_bounds__(NTT, NTT == 256 ? 2 : 1) void qk_bf16_rows_kernel(
     // key tiles wholly above the diagonal: one contiguous run per row, each
     // wave writing whole rows with 1 KiB per store instruction
     const uint32_t ninf2 = 0xff80ff80u;
-    const int c0 = n_compute * BT;
-    const int nv = (Lk - c0) / 8;                 // 16-byte vectors per row (Lk % 8 == 0)
-    for (int r = wave; r < BQ; r += NT / 64)
-        for (int v = lane; v < nv; v += 64)
+    const int c0 = max(t_lo, n_compute) * BT, c_end = min(Lk, t_hi * BT);
+    for (int r = wave; r < BQ && c0 < c_end; r += NT / 64) {
+        // 16-byte vectors from the row's first aligned element on, lanes placed in
+        // 128-byte lines as above, and the elements before and after them
+        const int row0 = r * Lk, m = (s_mis + row0 + c0) & 63;
+        const int head = RAG ? max(0, min((8 - (m & 7)) & 7, c_end - c0)) : 0;
+        const int c1 = c0 + head, nv = (c_end - c1) / 8;
+        for (int v = lane - (RAG ? ((m + head) & 63) >> 3 : 0); v < nv; v += 64)
             __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{ninf2, ninf2, ninf2, ninf2}, sr,
-                static_cast<uint32_t>((r * Lk + c0 + 8 * v) * 2), 0, kStoreAux);
+                !RAG || v >= 0 ? static_cast<uint32_t>((row0 + c1 + 8 * v) * 2) : 0x80000000u, 0, kStoreAux);
+        if constexpr (ANY) {
+            // lanes 0..7: the elements before, 8..15: after
+            const int c = lane < 8 ? c0 + lane : c1 + 8 * max(nv, 0) + lane - 8;
+            const bool on = lane < 8 ? lane < head : lane < 16 && c < c_end;
+            __builtin_amdgcn_raw_buffer_store_b16(kBf16NegInf, sr,
+                on ? static_cast<uint32_t>((row0 + c) * 2) : 0x80000000u, 0, kStoreAux);
+        }
+    }
 }
 
 template <int BM, int BN, int BK>
@@ -469,20 +633,32 @@ bool qk_rows_ok(int64_t Lk, int64_t D, const void *S) {
            reinterpret_cast<uintptr_t>(S) % 16 == 0;
 }
 
+namespace {
+// rows of S on 128-byte lines
+bool qk_lines(int64_t Lk, const void *S) { return Lk % 64 == 0 && reinterpret_cast<uintptr_t>(S) % 128 == 0; }
+// Gathered dims (half the matrix work) pay only for long rows, where the masked
+// product no longer hides behind the stores: 32 heads, k = 64, us masked / gathered:
+// 4096 keys 232 / 249, 8192 841 / 792, without the mask 850 / 813 (8 heads x 8192:
+// 242 / 202).
+bool qk_gathered(int64_t base, int64_t Lk, int64_t D, int64_t k, const void *S) {
+    return D == 128 && k <= 64 && Lk >= 6144 && base >= 256 && qk_lines(Lk, S);
+}
+}  // namespace
+
 hipError_t launch_qk_rowstats_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *idx,
                                    int64_t batch, int64_t H, int64_t Hkv, int64_t Lq, int64_t Lk,
                                    int64_t D, int64_t k, float scale, bool causal, uint16_t *S,
                                    float *rmax, float *rinv, hipStream_t stream) {
     if (!qk_rows_ok(Lk, D, S)) return hipErrorNotSupported;
-    dim3 grid(static_cast<unsigned>((Lq + rowk::BQ - 1) / rowk::BQ), static_cast<unsigned>(batch * H));
-    const bool wide = D == 128 && k <= 96;
-    auto kern = D == 64 ? qk_bf16_rows_kernel<64, 4, 1, 256, 128, true>
-              : k <= 64 ? qk_bf16_rows_kernel<128, 4, 1, 512, 256, true>
-              : k <= 96 ? qk_bf16_rows_kernel<128, 8, 2, 512, 256, true>
-                        : qk_bf16_rows_kernel<128, 8, 2, 256, 128, true>;
-    hipLaunchKernelGGL(kern, grid, dim3(wide ? 512 : 256), 0, stream, Q, Kc, idx, S,
+    const int64_t qb = (Lq + rowk::BQ - 1) / rowk::BQ;
+    dim3 grid(static_cast<unsigned>(qb), static_cast<unsigned>(batch * H));
+    // a block owns its rows' statistics: one share of the keys
+    auto kern = D == 64 ? qk_bf16_rows_kernel<64, 1, 256, 128, true>
+              : qk_gathered(qb * batch * H, Lk, D, k, S) ? qk_bf16_rows_kernel<128, 1, 512, 256, true, 0, true>
+                                                         : qk_bf16_rows_kernel<128, 2, 512, 256, true>;
+    hipLaunchKernelGGL(kern, grid, dim3(D == 128 ? 512 : 256), 0, stream, Q, Kc, idx, S,
                        static_cast<int>(H), static_cast<int>(Hkv), static_cast<int>(Lq),
-                       static_cast<int>(Lk), static_cast<int>(k), scale, causal ? 1 : 0, rmax, rinv);
+                       static_cast<int>(Lk), static_cast<int>(k), scale, causal ? 1 : 0, 1, rmax, rinv);
     return hipGetLastError();
 }
 
@@ -490,24 +666,39 @@ hipError_t launch_qk_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *
                           int64_t batch, int64_t H, int64_t Hkv, int64_t Lq, int64_t Lk,
                           int64_t D, int64_t k, float scale, bool causal, uint16_t *S,
                           hipStream_t stream) {
-    const bool rows_ok = qk_rows_ok(Lk, D, S);
-    if (rows_ok) {
-        dim3 grid(static_cast<unsigned>((Lq + rowk::BQ - 1) / rowk::BQ),
-                  static_cast<unsigned>(batch * H));
-        // up to 64 retained dims: one key strip per wave; more: 2x2 strips
-        // up to 96 retained dims: 256-key tiles, one 8-wave block per CU, so
-        // that every stored row piece is 512 bytes; more dims: 128-key tiles,
-        // two 4-wave blocks per CU (the heavier product overlaps better)
-        const bool wide = D == 128 && k <= 96;
-        auto kern = D == 64 ? qk_bf16_rows_kernel<64, 4, 1, 256, 128>
-                  : k <= 64 ? qk_bf16_rows_kernel<128, 4, 1, 512, 256>
-                  : k <= 96 ? qk_bf16_rows_kernel<128, 8, 2, 512, 256>
-                            : qk_bf16_rows_kernel<128, 8, 2, 256, 128>;
-        hipLaunchKernelGGL(kern, grid, dim3(wide ? 512 : 256), 0, stream, Q, Kc, idx, S,
-                           static_cast<int>(H), static_cast<int>(Hkv), static_cast<int>(Lq),
-                           static_cast<int>(Lk), static_cast<int>(k), scale, causal ? 1 : 0,
-                           nullptr, nullptr);
-        return hipGetLastError();
+    // 32-bit byte offsets into a block's 128 rows of S
+    if ((D == 64 || D == 128) && Lk <= (1 << 22)) {
+        // Blocks of 128-key tiles (two per CU) whose keys are split C ways up to
+        // 512 blocks, and in two for long rows on whole lines; us, D = 128:
+        //   1 x 32 heads x 1001 keys, k = 103: C = 1 / 2 / 4 22.6 / 19.0 / 22.2
+        //   1 x 32 x 2048, k = 64: C = 1 / 2 58 / 64;  1 x 40 x 2048: 93 / 78
+        //   1 x 32 x 4096, k = 64: C = 1 / 2 / 4 258 / 232 / 240
+        // 256-key tiles (one block per CU, 512-byte row pieces) for the longest rows
+        // (8192 keys, k = 128: 802 against 838) and where pieces are shifted to
+        // lines, from 1408 keys on (1 x 32 x 3000: 173 against 242 unshifted; 2 x 32 x
+        // 1001: 49 against 33; 2 x 32 x 1501: 94 against 106).
+        const int64_t qb = (Lq + rowk::BQ - 1) / rowk::BQ, base = qb * batch * H;
+        const bool lines = qk_lines(Lk, S), gathered = qk_gathered(base, Lk, D, k, S);
+        const bool shift = !lines && Lk >= 1408 && base >= 512;
+        const bool wide = D == 128 && (shift || (lines && Lk >= 6144 && base >= 256));
+        const int64_t tiles = (Lk + (wide ? 255 : 127)) / (wide ? 256 : 128);
+        int64_t C = wide || shift ? 1 : base < 512 ? (512 + base - 1) / base : lines && base > 512 && Lk >= 2048 ? 2 : 1;
+        if (C > tiles) C = tiles;
+        const int64_t tpc = (tiles + C - 1) / C;
+        C = (tiles + tpc - 1) / tpc;                      // no empty share
+        const dim3 grid(static_cast<unsigned>(qb * C), static_cast<unsigned>(batch * H));
+        auto run = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, dim3(wide ? 512 : 256), 0, stream, Q, Kc, idx, S,
+                               static_cast<int>(H), static_cast<int>(Hkv), static_cast<int>(Lq),
+                               static_cast<int>(Lk), static_cast<int>(k), scale, causal ? 1 : 0,
+                               static_cast<int>(C), nullptr, nullptr);
+            return hipGetLastError();
+        };
+        if (gathered) return run(qk_bf16_rows_kernel<128, 1, 512, 256, false, 0, true>);
+        if (shift) return wide ? run(qk_bf16_rows_kernel<128, 2, 512, 256, false, 2>) : run(qk_bf16_rows_kernel<64, 1, 256, 128, false, 2>);
+        if (wide) return run(qk_bf16_rows_kernel<128, 2, 512, 256>);
+        if (qk_rows_ok(Lk, D, S)) return D == 64 ? run(qk_bf16_rows_kernel<64, 1, 256, 128>) : run(qk_bf16_rows_kernel<128, 2, 256, 128>);
+        return D == 64 ? run(qk_bf16_rows_kernel<64, 1, 256, 128, false, 1>) : run(qk_bf16_rows_kernel<128, 2, 256, 128, false, 1>);
     }
     constexpr int BM = 128, BN = 128, BK = 32, WM = 2, WN = 2;
     dim3 grid(static_cast<unsigned>((Lk + BN - 1) / BN), static_cast<unsigned>((Lq + BM - 1) / BM),
