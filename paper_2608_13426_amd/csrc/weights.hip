@@ -64,7 +64,8 @@ __global__ __launch_bounds__(kRowThreads) void softmax_rowstats_kernel(
     // keys 0 .. nk-1 are kept (the causal mask keeps t <= i + Lk - Lq)
     const int64_t nk = !live ? 0 : causal ? max<int64_t>(0, min<int64_t>(Lk, i + Lk - Lq + 1)) : Lk;
     const int64_t nc = (nk + 7) / 8;
-    float m = -INFINITY, l = 0.f;
+    float m = -INFINITY;
+    double l = 0.0;
     for (int64_t c0 = sub; c0 < nc; c0 += 8 * kRowLanes) {
         uint4 q[8];
 #pragma unroll
@@ -95,10 +96,10 @@ __global__ __launch_bounds__(kRowThreads) void softmax_rowstats_kernel(
         }
         if (cm == -INFINITY) continue;                   // every key of the batch masked
         if (cm > m) {
-            l = m == -INFINITY ? 0.f : l * __expf(m - cm);
+            l = m == -INFINITY ? 0.0 : l * static_cast<double>(__expf(m - cm));
             m = cm;
         }
-        float l8[8] = {};                                // short chains, then a tree
+        float l8[8] = {};                                // chains of eight, then float64
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const uint32_t w[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
@@ -108,15 +109,19 @@ __global__ __launch_bounds__(kRowThreads) void softmax_rowstats_kernel(
                 l8[2 * e + 1] += __expf(__uint_as_float(w[e] & 0xffff0000u) - m);
             }
         }
-        l += ((l8[0] + l8[1]) + (l8[2] + l8[3])) + ((l8[4] + l8[5]) + (l8[6] + l8[7]));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) l += static_cast<double>(l8[e]);
     }
     const float mm = across16(m, [](float a, float b) { return fmaxf(a, b); });
-    l = m == -INFINITY ? 0.f : l * __expf(m - mm);
-    l = across16(l, [](float a, float b) { return a + b; });
+    l = m == -INFINITY ? 0.0 : l * static_cast<double>(__expf(m - mm));
+    l += dpp_f64<0xB1>(l);
+    l += dpp_f64<0x4E>(l);
+    l += dpp_f64<0x141>(l);
+    l += dpp_f64<0x140>(l);
     if (live && sub == 0) {
-        const bool empty = !(l > 0.f);
+        const bool empty = !(l > 0.0);
         rmax[row] = empty ? 0.f : mm;
-        rinv[row] = empty ? 0.f : 1.0f / l;
+        rinv[row] = empty ? 0.f : static_cast<float>(1.0 / l);
     }
 }
 
