@@ -557,7 +557,8 @@ hipError_t launch_select_tokens_grouped(const GemvGroups &G, int64_t B, hipStrea
 
 hipError_t launch_select_tokens(const void *X, bool bf16, int64_t B, int64_t K, int64_t ldx,
                                 int64_t k, int32_t *idx, hipStream_t stream) {
-    if (bf16 && K <= kToken16MaxK && reinterpret_cast<uintptr_t>(X) % 16 == 0 && ldx % 8 == 0) {
+    // up to 256 channels (a decode step's heads) every key is ranked directly
+    if (K > 256 && bf16 && K <= kToken16MaxK && reinterpret_cast<uintptr_t>(X) % 16 == 0 && ldx % 8 == 0) {
         if (K <= 8 * 256) return launch_token16<256, 8>(X, ldx, B, K, k, idx, stream);
         if (K <= 16 * 256) return launch_token16<256, 16>(X, ldx, B, K, k, idx, stream);
         if (K <= 16 * 512) return launch_token16<512, 16>(X, ldx, B, K, k, idx, stream);
