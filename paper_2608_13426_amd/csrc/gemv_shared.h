@@ -14,6 +14,7 @@ namespace rmm {
 // only the size is wanted), sets R and chunks, and returns its bytes.
 constexpr int kShareRange = 512;
 constexpr int kShareMaxB = 32;
+constexpr int kShareMaxRun = 4;      // ranges one product workgroup can take in turn
 struct ShareGroup {
     const uint16_t *X;      // [B][ldx] bf16, one token per sequence
     const uint16_t *W;      // [K][ldw] bf16, 16-byte aligned, ldw % 8 == 0
@@ -23,8 +24,9 @@ struct ShareGroup {
     int32_t *rows;          // [R][kShareRange] union rows of each range
     int32_t *cnt;           // [R] union size of each range
     uint16_t *xs;           // [R][32][kShareRange] activations over the union rows
-    float *P;               // [B][R][N] fp32 partials when R > 1
+    float *P;               // [B][RP][N] fp32 partials when RP > 1 (room for [B][R][N])
     int N, K, k, R, chunks;
+    int RM, RP;             // ranges per product workgroup (a run), runs: set by the launcher
     int64_t ldx, ldw, ldy;
     int first_o, first_u, first_p, first_r;
 };

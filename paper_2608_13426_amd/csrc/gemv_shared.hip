@@ -30,14 +30,14 @@
 //      in ascending order (a block scan), and the range's union rows and
 //      xs[b][row] (bf16, zeros past the union and for sequences that do not
 //      keep the row) go to the workspace;
-//   3. share_product_kernel, one workgroup per (range, column chunk: 128
+//   3. share_product_kernel, one workgroup per (run of 1, 2 or 4 ranges, column chunk: 128
 //      columns below eight sequences, 256 from eight on): the union rows of
 //      W stream through an LDS ring by LDS DMA (six slots of 32 rows, or
 //      four of the wider rows), W fragments come back with the
 //      transposing LDS read, xs fragments are loaded into registers with
-//      their stage; each range writes fp32 partials (or Y when there is one
-//      range);
-//   4. share_reduce_kernel adds the ranges' partials in range order.
+//      their stage; each run writes fp32 partials (or Y when there is one
+//      run);
+//   4. share_reduce_kernel adds the runs' partials in order.
 #include <type_traits>
 #include <utility>
 
@@ -219,7 +219,8 @@ __global__ __launch_bounds__(kUnionThreads) void share_union_kernel(ShareGroups 
     }
 }
 
-// 3. the range's product for CW_ columns: Y^T tile (columns x sequences).
+// 3. a run of ranges' product for CW_ columns: Y^T tile (columns x sequences),
+// their stages one after another through one ring.
 // The four waves take CW_/128 blocks of 32 columns each; the ring has NS_
 // slots of 32 staged rows (NS_ - 1 stages in flight).
 template <int N, typename F, int... I>
@@ -229,7 +230,7 @@ __device__ __forceinline__ void share_steps(F &&f, int st, int nst, std::integer
 }
 
 template <int CW_, int NS_>
-__global__ __launch_bounds__(sh::NT, (160 * 1024) / (NS_ * sh::RS * CW_ * 2 + 4 * sh::RG + 1024))
+__global__ __launch_bounds__(sh::NT, (160 * 1024) / (NS_ * sh::RS * CW_ * 2 + 4 * kShareMaxRun * sh::RG + 512))
 void share_product_kernel(ShareGroups G, int B) {
     using namespace sh;
     constexpr int ROWB = CW_ * 2;              // bytes per staged W row
@@ -241,7 +242,7 @@ void share_product_kernel(ShareGroups G, int B) {
     constexpr int DA = NS_ - 1;                // stages in flight ahead of the MFMAs
     constexpr int LPS = PER + RS / 16;         // vector loads per wave per stage (DMA + xs)
     static_assert(NB >= 1 && PER >= 1 && NS_ >= 3 && NS_ <= 8 && (DA - 1) * LPS < 64, "layout");
-    __shared__ int32_t rl[RG];
+    __shared__ int32_t rl[kShareMaxRun * RG];   // the run's union rows, each range padded to whole stages (-1)
     // one LDS object per ring slot: the compiler then sees that reading one
     // slot cannot alias the loads still landing in the others
     __shared__ __attribute__((aligned(1024))) char sl0[SLOT], sl1[SLOT], sl2[SLOT];
@@ -262,14 +263,23 @@ void share_product_kernel(ShareGroups G, int B) {
     const int gi = share_group(G, bid, [](const ShareGroup &q) { return q.first_p; });
     const ShareGroup &q = G.g[gi];
     const int local = bid - q.first_p;
-    const int r = local / q.chunks, chunk = local % q.chunks;
+    const int run = local / q.chunks, chunk = local % q.chunks;
     const int n0 = chunk * CW_;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int u = min(max(q.cnt[r], 0), RG);      // written by the union kernel
-    const int up = (u + RS - 1) / RS * RS;
-    const int nst = up / RS;
-    for (int p = tid; p < up; p += NT) rl[p] = p < u ? q.rows[static_cast<int64_t>(r) * RG + p] : 0;
+    // the run's ranges r0 .. : range i's stages are [end[i-1], end[i])
+    const int r0 = run * q.RM;
+    int end[kShareMaxRun], nst = 0;
+#pragma unroll
+    for (int i = 0; i < kShareMaxRun; ++i) {
+        const bool on = i < q.RM && r0 + i < q.R;
+        const int u = on ? min(max(q.cnt[r0 + i], 0), RG) : 0;      // written by the union kernel
+        const int up = (u + RS - 1) / RS * RS;
+        for (int p = tid; p < up; p += NT)
+            rl[nst * RS + p] = p < u ? q.rows[static_cast<int64_t>(r0 + i) * RG + p] : -1;
+        nst += up / RS;
+        end[i] = nst;
+    }
     __syncthreads();
 
     // W rows from column n0 on; columns past N read padding or the next row
@@ -277,10 +287,10 @@ void share_product_kernel(ShareGroups G, int B) {
     const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(q.W + n0), 0,
         static_cast<uint32_t>((static_cast<int64_t>(q.K) * q.ldw - n0) * 2), 0x00020000);
-    // the range's xs rows (sequences past B are never read)
+    // the run's xs rows (sequences past B are never read)
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t *>(q.xs + static_cast<int64_t>(r) * 32 * RG), 0,
-        static_cast<uint32_t>(32 * RG * 2), 0x00020000);
+        const_cast<uint16_t *>(q.xs + static_cast<int64_t>(r0) * 32 * RG), 0,
+        static_cast<uint32_t>(min(q.RM, q.R - r0) * 32 * RG * 2), 0x00020000);
     const uint32_t wrow = static_cast<uint32_t>(q.ldw) * 2u;
     constexpr uint32_t kOut = 0x80000000u;
     // DMA role: instruction e of the wave stages rows RPI*(PER*wave + e) +
@@ -294,7 +304,8 @@ void share_product_kernel(ShareGroups G, int B) {
             const int rr = row + drow;
             const int p = st * RS + rr;
             const uint32_t col = static_cast<uint32_t>(dpos ^ (4 * (rr & 3))) * 16u;
-            const uint32_t off = p < u ? static_cast<uint32_t>(rl[p]) * wrow + col : kOut;
+            const int32_t j = st < nst ? rl[p] : -1;
+            const uint32_t off = j >= 0 ? static_cast<uint32_t>(j) * wrow + col : kOut;
             lds_load16(wr, slot + row * ROWB, off);
         }
     };
@@ -304,9 +315,14 @@ void share_product_kernel(ShareGroups G, int B) {
     const uint32_t xoff = static_cast<uint32_t>(xb * RG + 8 * (lane >> 5)) * 2u;
     bf16x8_t xq[NS_][RS / 16];
     auto xload = [&](bf16x8_t (&d)[RS / 16], int st) {
+        // stage st of the run is stage st - end[i-1] of its range i
+        int row = st * RS;
+#pragma unroll
+        for (int i = 1; i < kShareMaxRun; ++i)
+            if (st >= end[i - 1]) row = i * 32 * RG + (st - end[i - 1]) * RS;
 #pragma unroll
         for (int ks = 0; ks < RS / 16; ++ks) {
-            const uint32_t off = xb < B && st < nst ? xoff + static_cast<uint32_t>(st * RS + ks * 16) * 2u : kOut;
+            const uint32_t off = xb < B && st < nst ? xoff + static_cast<uint32_t>(row + ks * 16) * 2u : kOut;
             d[ks] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
         }
     };
@@ -378,14 +394,14 @@ void share_product_kernel(ShareGroups G, int B) {
             for (int i = 0; i < 4; ++i) {
                 const int n = n0 + 32 * (wave * NB + j) + 8 * gq + 4 * (lane >> 5) + i;
                 if (n >= q.N) continue;
-                if (q.R == 1)
+                if (q.RP == 1)
                     q.Y[static_cast<int64_t>(b) * q.ldy + n] = f32_to_bf16(acc[j][4 * gq + i]);
                 else
-                    q.P[(static_cast<int64_t>(b) * q.R + r) * q.N + n] = acc[j][4 * gq + i];
+                    q.P[(static_cast<int64_t>(b) * q.RP + run) * q.N + n] = acc[j][4 * gq + i];
             }
 }
 
-// 4. Y[b][n] = the ranges' partials P[b][r][n] added in range order; a
+// 4. Y[b][n] = the runs' partials P[b][r][n] added in order; a
 // thread takes four consecutive columns of one sequence
 __global__ __launch_bounds__(sh::NT) void share_reduce_kernel(ShareGroups G, int B) {
     const int bid = static_cast<int>(blockIdx.x);
@@ -393,25 +409,25 @@ __global__ __launch_bounds__(sh::NT) void share_reduce_kernel(ShareGroups G, int
     const ShareGroup &q = G.g[gi];
     const int n4 = (q.N + 3) / 4;
     const int i = (bid - q.first_r) * sh::NT + static_cast<int>(threadIdx.x);
-    if (q.R < 2 || i >= B * n4) return;
+    if (q.RP < 2 || i >= B * n4) return;
     const int b = i / n4, n = 4 * (i % n4);
-    const float *p = q.P + static_cast<int64_t>(b) * q.R * q.N + n;
+    const float *p = q.P + static_cast<int64_t>(b) * q.RP * q.N + n;
     float s[4] = {0.f, 0.f, 0.f, 0.f};
     if (q.N % 4 == 0) {
         int r = 0;
-        for (; r + 8 <= q.R; r += 8) {
+        for (; r + 8 <= q.RP; r += 8) {
             float4 v[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = *reinterpret_cast<const float4 *>(p + static_cast<int64_t>(r + e) * q.N);
 #pragma unroll
             for (int e = 0; e < 8; ++e) { s[0] += v[e].x; s[1] += v[e].y; s[2] += v[e].z; s[3] += v[e].w; }
         }
-        for (; r < q.R; ++r) {
+        for (; r < q.RP; ++r) {
             const float4 v = *reinterpret_cast<const float4 *>(p + static_cast<int64_t>(r) * q.N);
             s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
         }
     } else {
-        for (int r = 0; r < q.R; ++r)
+        for (int r = 0; r < q.RP; ++r)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (n + e < q.N) s[e] += p[static_cast<int64_t>(r) * q.N + e];
@@ -444,17 +460,29 @@ size_t share_group_layout(int64_t B, int64_t N, int64_t K, void *ws, ShareGroup 
 }
 
 hipError_t launch_share_products(ShareGroups G, int64_t B, hipStream_t stream) {
-    int o = 0, un = 0, pr = 0, rd = 0;
+    int o = 0, un = 0, pr = 0, rd = 0, blocks = 0;
+    for (int i = 0; i < G.n; ++i) blocks += G.g[i].R * G.g[i].chunks;
+    // Ranges per product workgroup: longer runs pay the prologue and the partials
+    // less often, as long as enough workgroups are left.  A step in us (8B layer,
+    // 1664 workgroups at one range each from eight sequences on) at 1 / 2 / 4: B = 16
+    // 134.7 / 127.6 / 123.1, B = 32 163 / 148 / 138; 1B layer (464) 53.5 / 50.6 / 53.2;
+    // 70B layer (6528) 444 / 391 / 367.  Narrow tiles, B = 4, r = 0.5: 8B (3328) 113 /
+    // 106 / 110, 1B (928) 46.5 / 43.6 / 45.8, 70B (13056) 369 / 329 / 313.
+    const int rm = share_cols(B) == 256 ? (blocks >= 800 ? 4 : blocks >= 400 ? 2 : 1)
+                                        : (blocks >= 6000 ? 4 : blocks >= 800 ? 2 : 1);
+    static_assert(kShareMaxRun == 4, "longest run");
     for (int i = 0; i < G.n; ++i) {
         ShareGroup &q = G.g[i];
+        q.RM = rm;
+        q.RP = (q.R + rm - 1) / rm;
         q.first_o = o;
         o += static_cast<int>(B) * ((q.k + sh::NT - 1) / sh::NT);
         q.first_u = un;
         un += q.R;
         q.first_p = pr;
-        pr += q.R * q.chunks;
+        pr += q.RP * q.chunks;
         q.first_r = rd;
-        if (q.R > 1) rd += (static_cast<int>(B) * ((q.N + 3) / 4) + sh::NT - 1) / sh::NT;
+        if (q.RP > 1) rd += (static_cast<int>(B) * ((q.N + 3) / 4) + sh::NT - 1) / sh::NT;
     }
     const int Bi = static_cast<int>(B);
     hipLaunchKernelGGL(share_offsets_kernel, dim3(static_cast<unsigned>(o)), dim3(sh::NT), 0, stream, G, Bi);
