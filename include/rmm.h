@@ -686,10 +686,9 @@ rmm_status_t rmm_decode_products(const rmm_decode_group_t *groups, int ngroups, 
  * B        : 1..32 sequences.
  * workspace: rmm_decode_products_shared_workspace_size(groups, ngroups, B)
  *            bytes (never 0), 256-byte aligned.
- * Four launches for all groups together: the range boundaries of each list,
- * the union of every 512-index range with the activations over it, the
- * products (fp32 partials per run of ranges), the fixed-order reduction of
- * the runs.
+ * Three launches for all groups together: the union of every 512-index range
+ * with the activations over it, the products (fp32 partials per run of
+ * ranges), the fixed-order reduction of the runs.
  * Errors   : as rmm_decode_products; UNSUPPORTED also for B > 32.
  */
 size_t rmm_decode_products_shared_workspace_size(const rmm_decode_group_t *groups, int ngroups,

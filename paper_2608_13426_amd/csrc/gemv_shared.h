@@ -10,7 +10,7 @@ namespace rmm {
 // Decode products of B <= kShareMaxB sequences over the union of their sets
 // (each kept weight row read once for all of them).  The contraction axis is
 // cut into ranges of kShareRange indices; the layout function carves a
-// group's workspace (pos, rows, cnt, xs, P) from ws (which may be null when
+// group's workspace (rows, cnt, xs, P) from ws (which may be null when
 // only the size is wanted), sets R and chunks, and returns its bytes.
 constexpr int kShareRange = 512;
 constexpr int kShareMaxB = 32;
@@ -20,7 +20,6 @@ struct ShareGroup {
     const uint16_t *W;      // [K][ldw] bf16, 16-byte aligned, ldw % 8 == 0
     const int32_t *idx;     // [B][k] ascending lists
     uint16_t *Y;            // [B][ldy] bf16
-    int32_t *pos;           // [B][R+1] list position of each range boundary
     int32_t *rows;          // [R][kShareRange] union rows of each range
     int32_t *cnt;           // [R] union size of each range
     uint16_t *xs;           // [R][32][kShareRange] activations over the union rows
@@ -28,7 +27,7 @@ struct ShareGroup {
     int N, K, k, R, chunks;
     int RM, RP;             // ranges per product workgroup (a run), runs: set by the launcher
     int64_t ldx, ldw, ldy;
-    int first_o, first_u, first_p, first_r;
+    int first_u, first_p, first_r;
 };
 struct ShareGroups {
     ShareGroup g[kMaxGemvGroups];

@@ -17,27 +17,24 @@
 // exact zeros); the order of the additions differs from the per-sequence
 // kernel, so results agree within rounding, not bit for bit.
 //
-// The contraction axis is cut into ranges of kShareRange indices.  Four
+// The contraction axis is cut into ranges of kShareRange indices.  Three
 // launches:
-//   1. share_offsets_kernel: for every sequence and range boundary, the first
-//      position of the sequence's (ascending) list at or past it -- each list
-//      position writes the boundaries between its predecessor and itself, so
-//      every entry has one writer and no memory needs clearing;
-//   2. share_union_kernel, one workgroup per range: the sequences'
+//   1. share_union_kernel, one workgroup per range: a wave per sequence finds
+//      its (ascending) list's positions of the range's ends, the sequences'
 //      activations over the range are staged in LDS, the members of each
 //      sequence's sub-list set bits of a per-index sequence mask in LDS
 //      (atomic OR: order-free), the indices with a nonzero mask are compacted
 //      in ascending order (a block scan), and the range's union rows and
 //      xs[b][row] (bf16, zeros past the union and for sequences that do not
 //      keep the row) go to the workspace;
-//   3. share_product_kernel, one workgroup per (run of 1, 2 or 4 ranges, column chunk: 128
+//   2. share_product_kernel, one workgroup per (run of 1, 2 or 4 ranges, column chunk: 128
 //      columns below eight sequences, 256 from eight on): the union rows of
 //      W stream through an LDS ring by LDS DMA (six slots of 32 rows, or
 //      four of the wider rows), W fragments come back with the
 //      transposing LDS read, xs fragments are loaded into registers with
 //      their stage; each run writes fp32 partials (or Y when there is one
 //      run);
-//   4. share_reduce_kernel adds the runs' partials in order.
+//   3. share_reduce_kernel adds the runs' partials in order.
 #include <type_traits>
 #include <utility>
 
@@ -77,30 +74,43 @@ __device__ __forceinline__ int share_group(const ShareGroups &G, int bid, F firs
     return g;
 }
 
-// 1. list positions of the range boundaries: pos[b][r] = first t with
-// I_b[t] >= r * RG (pos[b][R] = k)
-__global__ __launch_bounds__(sh::NT) void share_offsets_kernel(ShareGroups G, int B) {
-    const int bid = static_cast<int>(blockIdx.x);
-    const int gi = share_group(G, bid, [](const ShareGroup &q) { return q.first_o; });
-    const ShareGroup &q = G.g[gi];
-    const int per = (q.k + sh::NT - 1) / sh::NT;     // workgroups per sequence
-    const int local = bid - q.first_o;
-    const int b = local / per;
-    const int t = (local % per) * sh::NT + static_cast<int>(threadIdx.x);
-    if (b >= B || t >= q.k) return;
-    const int32_t *I = q.idx + static_cast<int64_t>(b) * q.k;
-    int32_t *pos = q.pos + static_cast<int64_t>(b) * (q.R + 1);
-    // indices outside [0, K) are clamped (lists are required to lie within it)
-    auto range_of = [&](int32_t j) { return min(max(j, 0), q.K - 1) / sh::RG; };
-    const int hi = range_of(I[t]);
-    const int lo = t == 0 ? -1 : range_of(I[t - 1]);
-    for (int r = lo + 1; r <= hi; ++r) pos[r] = t;
-    if (t == q.k - 1)
-        for (int r = hi + 1; r <= q.R; ++r) pos[r] = q.k;
+// Positions of the first entries >= j0 and >= j1 of the ascending lists Ia and
+// Ib of k (Ib null: 0 and 0), by the whole wave: 64 probes a round for each, so
+// two rounds up to 4096 entries and three up to 262144.  A list that is not
+// ascending gives some position in 0..k.
+__device__ __forceinline__ void share_bounds(const int32_t *__restrict__ Ia, const int32_t *__restrict__ Ib,
+                                             int k, int j0, int j1, int lane, int (&t)[4]) {
+    int n[4] = {k, k, Ib ? k : 0, Ib ? k : 0};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = 0;
+    while ((n[0] | n[1] | n[2] | n[3]) > 0) {
+        int v[4], step[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            step[e] = (n[e] + 63) / 64;
+            v[e] = lane * step[e] < n[e] ? (e < 2 ? Ia : Ib)[t[e] + lane * step[e]] : 0;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // probes before the position
+            const int c = __popcll(__ballot(lane * step[e] < n[e] && v[e] < (e & 1 ? j1 : j0)));
+            if (c == 0) {
+                n[e] = 0;
+            } else {
+                const int skip = (c - 1) * step[e] + 1;
+                n[e] = min(step[e] - 1, n[e] - skip);
+                t[e] += skip;
+            }
+        }
+    }
 }
 
-// 2. the union of the B sub-lists of one range, and xs over it (1024
-// threads: the work of one range is a few dependent LDS passes)
+// 1. the union of the B sub-lists of one range, and xs over it (1024
+// threads: the work of one range is a few dependent LDS passes).  The range's
+// positions in the lists are found here, two or three rounds of one load, rather
+// than by a launch of their own before it (a step in us, with that launch / without:
+// 1B layer, r = 0.5, one sequence 35.0 / 32.9, 16 49.4 / 48.4, 32 56.4 / 57.0; 8B layer
+// 64.2 / 62.1, 121.7 / 120.9, 137.4 / 138.5).
 constexpr int kUnionThreads = 1024;
 __global__ __launch_bounds__(kUnionThreads) void share_union_kernel(ShareGroups G, int B) {
     using namespace sh;
@@ -119,18 +129,52 @@ __global__ __launch_bounds__(kUnionThreads) void share_union_kernel(ShareGroups 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j0 = r * RG, nj = min(RG, q.K - j0);
     for (int i = tid; i < RG; i += UT) mask[i] = 0u;
-    // the sub-lists of the range (clamped, so that a list that breaks the
-    // ascending precondition still reads inside itself) and their offsets
-    if (wave == 0) {
-        int len = 0;
-        if (lane < B) {
-            const int32_t *pos = q.pos + static_cast<int64_t>(lane) * (q.R + 1);
-            const int t0 = min(max(pos[r], 0), q.k);
-            const int t1 = min(max(pos[r + 1], t0), q.k);
-            beg[lane] = t0;
-            len = t1 - t0;
+    // each sequence's activations over the range, 16 bytes at a time (X rows
+    // are 16-byte aligned and j0 is a multiple of 8); past K: zeros, never kept.
+    // Loaded before the search, stored after it.
+    constexpr int cpr = RG / 8, XV = kShareMaxB * cpr / UT;
+    uint4 xv[XV];
+#pragma unroll
+    for (int u = 0; u < XV; ++u) {
+        const int i = tid + u * UT, b = i / cpr, c = i % cpr;
+        xv[u] = uint4{0, 0, 0, 0};
+        if (i < B * cpr) {
+            const uint16_t *x = q.X + static_cast<int64_t>(b) * q.ldx + j0 + 8 * c;
+            if (8 * c + 8 <= nj) {
+                xv[u] = *reinterpret_cast<const uint4 *>(x);
+            } else {
+                uint32_t w[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t a = 8 * c + 2 * e < nj ? x[2 * e] : 0u, h = 8 * c + 2 * e + 1 < nj ? x[2 * e + 1] : 0u;
+                    w[e] = a | h << 16;
+                }
+                xv[u] = uint4{w[0], w[1], w[2], w[3]};
+            }
         }
-        int incl = len;
+    }
+    // the sub-lists of the range
+    static_assert(kShareMaxB == 2 * UW, "two lists a wave");
+    if (wave < B) {
+        const int32_t *I = q.idx + static_cast<int64_t>(wave) * q.k;
+        const bool two = wave + UW < B;
+        int t[4];
+        share_bounds(I, two ? I + static_cast<int64_t>(UW) * q.k : nullptr, q.k, j0, j0 + RG, lane, t);
+        if (lane == 0) {
+            beg[wave] = t[0];
+            seg[wave + 1] = max(t[1] - t[0], 0);
+            if (two) {
+                beg[wave + UW] = t[2];
+                seg[wave + UW + 1] = max(t[3] - t[2], 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < XV; ++u)
+        if (tid + u * UT < B * cpr) *reinterpret_cast<uint4 *>(&xr[8 * (tid + u * UT)]) = xv[u];
+    __syncthreads();
+    if (wave == 0) {                               // lengths -> prefix sums
+        int incl = lane < B ? seg[lane + 1] : 0;
 #pragma unroll
         for (int sft = 1; sft < 32; sft <<= 1) {
             const int v = __shfl_up(incl, sft);
@@ -138,20 +182,6 @@ __global__ __launch_bounds__(kUnionThreads) void share_union_kernel(ShareGroups 
         }
         if (lane < B) seg[lane + 1] = incl;
         if (lane == 0) seg[0] = 0;
-    }
-    // each sequence's activations over the range, 16 bytes at a time (X rows
-    // are 16-byte aligned and j0 is a multiple of 8); past K: zeros, never kept
-    const int cpr = RG / 8;
-    for (int i = tid; i < B * cpr; i += UT) {
-        const int b = i / cpr, c = i % cpr;
-        const uint16_t *x = q.X + static_cast<int64_t>(b) * q.ldx + j0 + 8 * c;
-        uint16_t *d = &xr[b * RG + 8 * c];
-        if (8 * c + 8 <= nj) {
-            *reinterpret_cast<uint4 *>(d) = *reinterpret_cast<const uint4 *>(x);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) d[e] = 8 * c + e < nj ? x[e] : 0;
-        }
     }
     __syncthreads();
     // every entry of every sub-list sets its sequence's bit (atomic OR:
@@ -219,7 +249,7 @@ __global__ __launch_bounds__(kUnionThreads) void share_union_kernel(ShareGroups 
     }
 }
 
-// 3. a run of ranges' product for CW_ columns: Y^T tile (columns x sequences),
+// 2. a run of ranges' product for CW_ columns: Y^T tile (columns x sequences),
 // their stages one after another through one ring.
 // The four waves take CW_/128 blocks of 32 columns each; the ring has NS_
 // slots of 32 staged rows (NS_ - 1 stages in flight).
@@ -401,7 +431,7 @@ void share_product_kernel(ShareGroups G, int B) {
             }
 }
 
-// 4. Y[b][n] = the runs' partials P[b][r][n] added in order; a
+// 3. Y[b][n] = the runs' partials P[b][r][n] added in order; a
 // thread takes four consecutive columns of one sequence
 __global__ __launch_bounds__(sh::NT) void share_reduce_kernel(ShareGroups G, int B) {
     const int bid = static_cast<int>(blockIdx.x);
@@ -442,25 +472,25 @@ __global__ __launch_bounds__(sh::NT) void share_reduce_kernel(ShareGroups G, int
 size_t share_group_layout(int64_t B, int64_t N, int64_t K, void *ws, ShareGroup *q) {
     auto a256 = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
     const int64_t R = (K + kShareRange - 1) / kShareRange;
-    const size_t pos = a256(static_cast<size_t>(B * (R + 1)) * 4);
+    // unused; part of the size a caller has been asked for since the first version
+    const size_t head = a256(static_cast<size_t>(B * (R + 1)) * 4);
     const size_t rows = a256(static_cast<size_t>(R * kShareRange) * 4);
     const size_t cnt = a256(static_cast<size_t>(R) * 4);
     const size_t xs = a256(static_cast<size_t>(R * 32 * kShareRange) * 2);
     const size_t part = R > 1 ? a256(static_cast<size_t>(B * R * N) * 4) : 0;
     // addresses formed as integers: ws may be null when only the size is asked
     const uintptr_t p = reinterpret_cast<uintptr_t>(ws);
-    q->pos = reinterpret_cast<int32_t *>(p);
-    q->rows = reinterpret_cast<int32_t *>(p + pos);
-    q->cnt = reinterpret_cast<int32_t *>(p + pos + rows);
-    q->xs = reinterpret_cast<uint16_t *>(p + pos + rows + cnt);
-    q->P = R > 1 ? reinterpret_cast<float *>(p + pos + rows + cnt + xs) : nullptr;
+    q->rows = reinterpret_cast<int32_t *>(p + head);
+    q->cnt = reinterpret_cast<int32_t *>(p + head + rows);
+    q->xs = reinterpret_cast<uint16_t *>(p + head + rows + cnt);
+    q->P = R > 1 ? reinterpret_cast<float *>(p + head + rows + cnt + xs) : nullptr;
     q->R = static_cast<int>(R);
     q->chunks = static_cast<int>((N + share_cols(B) - 1) / share_cols(B));
-    return pos + rows + cnt + xs + part;
+    return head + rows + cnt + xs + part;
 }
 
 hipError_t launch_share_products(ShareGroups G, int64_t B, hipStream_t stream) {
-    int o = 0, un = 0, pr = 0, rd = 0, blocks = 0;
+    int un = 0, pr = 0, rd = 0, blocks = 0;
     for (int i = 0; i < G.n; ++i) blocks += G.g[i].R * G.g[i].chunks;
     // Ranges per product workgroup: longer runs pay the prologue and the partials
     // less often, as long as enough workgroups are left.  A step in us (8B layer,
@@ -475,8 +505,6 @@ hipError_t launch_share_products(ShareGroups G, int64_t B, hipStream_t stream) {
         ShareGroup &q = G.g[i];
         q.RM = rm;
         q.RP = (q.R + rm - 1) / rm;
-        q.first_o = o;
-        o += static_cast<int>(B) * ((q.k + sh::NT - 1) / sh::NT);
         q.first_u = un;
         un += q.R;
         q.first_p = pr;
@@ -485,12 +513,10 @@ hipError_t launch_share_products(ShareGroups G, int64_t B, hipStream_t stream) {
         if (q.RP > 1) rd += (static_cast<int>(B) * ((q.N + 3) / 4) + sh::NT - 1) / sh::NT;
     }
     const int Bi = static_cast<int>(B);
-    hipLaunchKernelGGL(share_offsets_kernel, dim3(static_cast<unsigned>(o)), dim3(sh::NT), 0, stream, G, Bi);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(share_union_kernel, dim3(static_cast<unsigned>(un)), dim3(kUnionThreads), 0, stream,
                        G, Bi);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     if (share_cols(B) == 256)
         hipLaunchKernelGGL((share_product_kernel<256, 4>), dim3(static_cast<unsigned>(pr)), dim3(sh::NT), 0,
                            stream, G, Bi);
