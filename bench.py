@@ -114,7 +114,7 @@ DECODE_TRAFFIC = {"sources": [os.path.join(CSRC, f) for f in ("gemv.hip", "kerne
                                   + (160329.72 * 2.0 + 3948.19 + 1993.0 * 2.0 + 84.0)
                                   + (213691.84 * 2.0 + 4222.14 + 2121.0 * 2.0 + 84.0)) / 4 * 1024)}
 # per rmm_decode_products_shared call at B = 16, r = 0.5 on the 8B groups:
-# its four kernels (boundaries, union pass, product, range reduction)
+# its three kernels (union pass, product, reduction of the runs)
 SHARED_TRAFFIC = {"sources": [os.path.join(CSRC, f) for f in ("gemv_shared.hip", "gemv_shared.h",
                                                               "kernels.h", "device_common.h")]
                   + [BUILD_SCRIPT],
@@ -1425,7 +1425,7 @@ def main():
                   "rmm_decode_products_shared reads each row of the union of the B sets once and "
                   "multiplies all sequences on the matrix cores; torch's dense product of the same "
                   "tokens; each a replayed graph of 10 back-to-back calls",
-            "kernels": ["share_offsets_kernel", "share_union_kernel",
+            "kernels": ["share_union_kernel",
                         "share_product_kernel<128, 6> (B < 8), <256, 4> (B >= 8)", "share_reduce_kernel"],
             "per_batch_ratio": {f"B{x['batch']}@{x['r']}": {k: (round(v, 3) if isinstance(v, float) else v)
                                                            for k, v in x.items()} for x in recs},
@@ -1476,7 +1476,7 @@ def main():
                   "token rows, causal row tiles trimmed); dense = torch softmax + torch P @ V; "
                   f"{a.H} q / {a.Hkv} kv heads, seq {wk.M}, d={a.D}",
             "kernels": ["softmax_rowstats_kernel", "score_tile_kernel (softmax variant)",
-                        "score_finalize_kernel", "select_kernel", "gemm_kmajor_tr_kernel (256x128)"],
+                        "score_finalize_kernel", "select_kernel", "gemm_kmajor_mid_kernel (128x128)"],
             "per_ratio": {str(r): {k: (round(v, 3) if isinstance(v, float) else v)
                                    for k, v in rec.items()} for r, rec in pc.items()},
             "speedup_vs_r1": round(c_1["reduced_us"] / c_h["reduced_us"], 3) if c_1 and c_h else None,
