@@ -86,42 +86,42 @@ def _sources(main):
 # file, the shared headers and the build script) is the one it was measured
 # with, and for the same launch mix; re-run the counters after any change.
 GEMM_TRAFFIC = {"sources": _sources("gemm.hip"),
-                "sha256": "2f2c9f14c1ee2a707e502647b0ed6082ecc70473c4370aa1de688d67103f4f47",
+                "sha256": "68ac2b7ad27c91221c97636ed8c27456ab2c122eefb3902319df8527e0e8c286",
                 "mix": "layer_8b r=0.25,0.5,0.75,1.0 grouped",
-                "bytes": round((399447.85 * 2.0 + 172169.57) * 1024)}
+                "bytes": round((399451.23 * 2.0 + 172205.58) * 1024)}
 # per fused attention call: attn_fwd_kernel (mean over the four ratios' kernels)
 # plus attn_compact_k_kernel
 ATTN_TRAFFIC = {"sources": _sources("attn.hip"),
-                "sha256": "2ef66f0b47540990067c3d74bdff9c5089cd7921d90f6202cdc486f4c9858b0d",
+                "sha256": "75cb10788b12ed82b426504dd6f8518ef879e79f71f7bbd66d905d2950e631e6",
                 "mix": "layer_8b r=0.25,0.5,0.75,1.0",
-                "bytes": round((103628.45 * 2.0 + 65550.75 + 8249.02 * 2.0 + 40960.00) * 1024)}
+                "bytes": round((103628.57 * 2.0 + 65550.01 + 8249.03 * 2.0 + 40960.00) * 1024)}
 # per rmm_rmsnorm_kmajor call (8192 x 4096, the same whatever r):
 # rms_block_kmajor_kernel and its score_finalize_grouped_kernel
 NORM_TRAFFIC = {"sources": _sources("norm.hip") + [os.path.join(CSRC, "score.hip")],
-                "sha256": "0340673358c97aa4fbe9598a3ef098cffc971f6775443e358ce25fb38375a34e",
+                "sha256": "79fe0c69964059ec38392903ab8f2fb268e3151519f1ec51fc89194bfb724c5f",
                 "mix": "layer_8b attn_in,mlp_in",
-                "bytes": round((33033.05 * 2.0 + 74159.67 + 4115.00 * 2.0 + 32.00) * 1024)}
+                "bytes": round((33033.05 * 2.0 + 74192.68 + 4115.00 * 2.0 + 32.00) * 1024)}
 
 # per rmm_decode_products call of the batch-1 decode step (the four 8B
 # groups; mean over the four ratios): gemv_partial_grouped_kernel and
 # gemv_reduce_grouped_kernel
 DECODE_TRAFFIC = {"sources": [os.path.join(CSRC, f) for f in ("gemv.hip", "kernels.h", "device_common.h")]
                   + [BUILD_SCRIPT],
-                  "sha256": "40da861c585557e8e1d6f6498bd11aa8d6d194f9f5d21c30863040a4de695740",
+                  "sha256": "6b225f92ec31b39168f1a0be790ba59d66188460e2f01631e19cf5a94e2a2dbc",
                   "mix": "layer_8b r=0.25,0.5,0.75,1.0 B=1",
-                  "bytes": round(((53592.86 * 2.0 + 2661.30 + 1349.0 * 2.0 + 84.0)
-                                  + (106951.50 * 2.0 + 3431.99 + 1733.0 * 2.0 + 84.0)
-                                  + (160329.72 * 2.0 + 3948.19 + 1993.0 * 2.0 + 84.0)
-                                  + (213691.84 * 2.0 + 4222.14 + 2121.0 * 2.0 + 84.0)) / 4 * 1024)}
+                  "bytes": round(((53593.4 * 2.0 + 2661.2 + 1349.0 * 2.0 + 84.0)
+                                  + (106949.4 * 2.0 + 3430.0 + 1733.0 * 2.0 + 84.0)
+                                  + (160329.0 * 2.0 + 3947.9 + 1993.0 * 2.0 + 84.0)
+                                  + (213691.9 * 2.0 + 4223.7 + 2121.0 * 2.0 + 84.0)) / 4 * 1024)}
 # per rmm_decode_products_shared call at B = 16, r = 0.5 on the 8B groups:
 # its three kernels (union pass, product, reduction of the runs)
 SHARED_TRAFFIC = {"sources": [os.path.join(CSRC, f) for f in ("gemv_shared.hip", "gemv_shared.h",
                                                               "kernels.h", "device_common.h")]
                   + [BUILD_SCRIPT],
-                  "sha256": "7c312c2936bb3855686f59ad095ab0d5a6bfa8657bc397231fe60e4724f12af6",
+                  "sha256": "c91a9a5074d75cbda43957970ce5194c26ef2cfa43cff701c36445623b487c3d",
                   "mix": "layer_8b B=16 r=0.5",
-                  "bytes": round((483.0 * 2.0 + 24.5 + 939.6 * 2.0 + 937.6 + 217030.5 * 2.0 + 26646.8
-                                  + 13333.0 * 2.0 + 1344.1) * 1024)}
+                  "bytes": round((2748.3 * 2.0 + 937.5 + 217373.0 * 2.0 + 6656.9
+                                  + 3351.0 * 2.0 + 1344.0) * 1024)}
 
 
 def sources_sha256(paths):
@@ -1429,13 +1429,13 @@ def main():
                         "share_product_kernel<128, 6> (B < 8), <256, 4> (B >= 8)", "share_reduce_kernel"],
             "per_batch_ratio": {f"B{x['batch']}@{x['r']}": {k: (round(v, 3) if isinstance(v, float) else v)
                                                            for k, v in x.items()} for x in recs},
-            "roofline": {"bound": "hbm", "kernel": "rmm_decode_products_shared (all four kernels), B=16 "
+            "roofline": {"bound": "hbm", "kernel": "rmm_decode_products_shared (all three kernels), B=16 "
                                                    f"r={HEADLINE_R}",
                          "achieved": round(head["shared_gbs"], 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                          "frac": round(head["shared_gbs"] / PEAK_HBM_GBS, 4),
                          "bytes_basis": "the union rows of every W once + the tokens and outputs",
                          "traffic": recorded_traffic(SHARED_TRAFFIC, f"{wk.name} B=16 r={HEADLINE_R}"),
-                         "traffic_unit": "HBM bytes per call (FETCH_SIZE + WRITE_SIZE, all four kernels)"},
+                         "traffic_unit": "HBM bytes per call (FETCH_SIZE + WRITE_SIZE, all three kernels)"},
         }
     if not (args.no_pv_chain and args.no_pv):
         # the value-product records take the layer's causal scores at the
