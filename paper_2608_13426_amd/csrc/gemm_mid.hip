@@ -179,14 +179,18 @@ __global__ __launch_bounds__(WM *WN * 64, WM *WN / 4) void gemm_kmajor_mid_kerne
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.f;
 
-    // a barrier that does not wait for the loads still landing in LDS; every
-    // step issues one stage of loads (past the end: zeros), so the wait before
-    // it is a fixed count
+    // a barrier that does not wait for the loads still landing in LDS, only for
+    // this wave's own LDS reads: the slot they read is refilled by the other
+    // waves right after it.  Every step issues one stage of loads (past the
+    // end: zeros), so the vmcnt wait before it is a fixed count.
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     using I3 = std::integral_constant<int, 3>;
-    auto barrier = []() { asm volatile("s_barrier" ::: "memory"); };
+    auto barrier = []() {
+        __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+        asm volatile("s_barrier" ::: "memory");
+    };
 
     for (int seg = 0; seg < kk; seg += kMidSeg) {
         const int ks_n = min(kMidSeg, kk - seg);
