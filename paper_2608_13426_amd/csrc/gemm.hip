@@ -558,9 +558,13 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_kmajor_tr_kernel(
 
     const int nT = (kk + BKS - 1) / BKS;
     int32_t r[2 * PPW];
-    // a barrier that orders this wave's LDS accesses around it but, unlike
-    // __syncthreads(), does not wait for the loads still landing in LDS
-    auto barrier = []() { asm volatile("s_barrier" ::: "memory"); };
+    // a barrier that waits for this wave's own LDS reads (the slot they read is
+    // refilled by the other waves right after it) but, unlike
+    // __syncthreads(), not for the loads still landing in LDS
+    auto barrier = []() {
+        __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+        asm volatile("s_barrier" ::: "memory");
+    };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;

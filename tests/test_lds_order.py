@@ -92,7 +92,7 @@ def test_pending_reads_are_found():
     assert reads_in_flight(carried) == [1]
 
 
-@pytest.mark.parametrize("source", ["gemm_mid.hip", "gemv_shared.hip", "attn.hip", "attn_few.hip", "qk.hip"])
+@pytest.mark.parametrize("source", ["gemm.hip", "gemm_mid.hip", "gemv_shared.hip", "attn.hip", "attn_few.hip", "qk.hip"])
 def test_no_lds_read_in_flight_at_a_barrier(source, tmp_path):
     asm = tmp_path / "out.s"
     subprocess.run([build.HIPCC, *build.CFLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source),
