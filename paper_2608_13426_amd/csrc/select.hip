@@ -150,6 +150,10 @@ __global__ __launch_bounds__(NT) void select_rank_kernel(const void *__restrict_
     const int t = tid >> 2, part = tid & 3;
     const void *e = static_cast<const char *>(src) + static_cast<int64_t>(blockIdx.x) * ld * esize;
     int32_t *out = idx + static_cast<int64_t>(blockIdx.x) * k;
+    if (k == K) {                       // everything is kept (512 units of 152: 2.3 us; 8.1 when ranked)
+        if (tid < K) out[tid] = tid;
+        return;
+    }
     if (tid < KP) keys[tid] = tid < K ? load_key<SRC>(e, tid) : 0ull;
     __syncthreads();
     const uint64_t u = keys[t];
