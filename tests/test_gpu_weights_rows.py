@@ -1,6 +1,6 @@
 """Row statistics of the attention weights at the edges of a row group's batches
-(16 lanes of eight 16-byte loads: 1024 keys), with fully masked and all -inf
-rows, against float64 softmax."""
+(16 or 64 lanes of eight 16-byte loads: 1024 or 4096 keys), with fully masked and
+all -inf rows, against float64 softmax."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +14,8 @@ pytestmark = gpu
 @pytest.mark.parametrize("U,Lq,Lk,causal", [
     (1, 1, 1, True), (3, 5, 7, False), (2, 17, 8, True), (1, 40, 129, True), (1, 3, 1024, False),
     (2, 9, 1025, False), (1, 20, 1040, True), (1, 2100, 2050, True),
+    (3, 701, 1025, True), (5, 420, 1031, False),     # 16 lanes per row, second batch of a few keys
+    (2, 3, 4097, False), (1, 33, 4101, True), (7, 1, 513, True),    # a wave per row, one batch and two
 ])
 def test_weights_row_statistics(U, Lq, Lk, causal):
     dev = require_gpu()
