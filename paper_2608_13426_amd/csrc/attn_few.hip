@@ -102,7 +102,10 @@ __global__ __launch_bounds__(GH *KS * 64) void attn_few_kernel(
 
     const uint16_t *Kh = Kc + (static_cast<int64_t>(b) * Hkv + gk) * Lk * D;
     const uint16_t *Vh = V + (static_cast<int64_t>(b) * Hkv + gk) * Lk * D;
-    const int n_tiles = (Lk + TK - 1) / TK;
+    // no row of the block keeps a key at or past kend: those are staged as zeros
+    // (a masked key's weight is zero, but 0 * infinity is not), whole tiles skipped
+    const int kend = causal ? max(0, min(Lk, min(q0 + TQ, Lq) + Lk - Lq)) : Lk;
+    const int n_tiles = (kend + TK - 1) / TK;
     const int t_begin = s * tps, t_end = min(n_tiles, t_begin + tps);
 
     // DMA role: instruction u of the wave fills rows 4j .. 4j+3 of the stage,
@@ -119,8 +122,8 @@ __global__ __launch_bounds__(GH *KS * 64) void attn_few_kernel(
     }
     auto dma = [&](char *slot, int t) __attribute__((always_inline)) {
         // tiles past the split's end read nothing and stage zeros
-        const int t0 = __builtin_amdgcn_readfirstlane(min(t * TK, Lk));
-        const int rows = __builtin_amdgcn_readfirstlane(t < t_end ? min(TK, Lk - t0) : 0);
+        const int t0 = __builtin_amdgcn_readfirstlane(min(t * TK, kend));
+        const int rows = __builtin_amdgcn_readfirstlane(t < t_end ? min(TK, kend - t0) : 0);
         const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t *>(Kh + static_cast<int64_t>(t0) * D), 0, static_cast<uint32_t>(rows * ROWB), 0x00020000);
         const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(GH *KS * 64) void attn_few_kernel(
 
     auto tile = [&](const char *slot, int t) __attribute__((always_inline)) {
         const int t0 = t * TK + TS * kw;
-        if (t0 >= Lk) return;                           // wave-uniform
+        if (t0 >= kend) return;                         // wave-uniform
         f32x4_t sc[2];
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb) {

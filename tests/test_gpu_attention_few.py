@@ -44,9 +44,12 @@ def _check(O, Qs, Ks, Vs, idx, causal, scale=None):
     (1, 8, 1, 16, 1500, 1.0, True, None),     # eight heads, all 16 rows
     (1, 20, 2, 5, 260, 0.001, False, 0.0),    # ten heads per kv head: two chunks; k = 1; zero scale
     (2, 4, 1, 13, 300, 0.5, False, 3.0),      # large scores: the maximum rises several times
-    (1, 4, 2, 15, 9, 0.25, True, None),       # more queries than keys: leading rows are zero
+    (1, 4, 2, 15, 9, 0.25, True, None),       # more queries than keys (the prefill kernel): leading rows are zero
     (1, 2, 1, 17, 200, 0.5, True, None),      # two blocks of query rows, the second of one
     (1, 4, 1, 70, 900, 0.8, True, None),      # five, several splits
+    (1, 4, 1, 256, 600, 1.0, True, None),     # causal: the last split is wholly masked for the early rows
+    (1, 4, 2, 224, 530, 1.0, True, None),     # ... pairs: and for some key tiles of a stage
+    (1, 2, 2, 200, 470, 1.0, True, None),     # ... one head per kv head
 ])
 def test_few_rows(b, H, Hkv, Lq, Lk, r, causal, scale):
     dev = require_gpu()
@@ -60,7 +63,8 @@ def test_few_rows(b, H, Hkv, Lq, Lk, r, causal, scale):
     assert torch.equal(O.view(torch.int16), O2.view(torch.int16))
 
 
-@pytest.mark.parametrize("b,H,Hkv,Lq,Lk", [(2, 8, 2, 8, 600), (1, 4, 4, 16, 150), (1, 2, 1, 8, 40)])
+@pytest.mark.parametrize("b,H,Hkv,Lq,Lk", [(2, 8, 2, 8, 600), (1, 4, 4, 16, 150), (1, 2, 1, 8, 40),
+                                           (1, 4, 1, 256, 1300), (1, 4, 2, 248, 1100), (1, 2, 2, 200, 900)])
 def test_few_rows_kmajor_same_bits(b, H, Hkv, Lq, Lk):
     """The K-major form holds the plain block's values bit for bit, with their energies."""
     dev = require_gpu()
@@ -95,3 +99,21 @@ def test_few_rows_ignore_nonfinite_dropped_dims():
     O2 = torch.empty_like(O)
     rmm.rmm_reduced_attention(*args, O2)
     assert torch.equal(O.view(torch.int16), O2.view(torch.int16))
+
+
+@pytest.mark.parametrize("H,Hkv,Lq,Lk", [(4, 1, 64, 400), (4, 2, 128, 700), (2, 2, 48, 300), (8, 1, 17, 200)])
+def test_few_rows_causal_future_values(H, Hkv, Lq, Lk):
+    """Non-finite value and key rows after a 16-row block's last visible key have no effect on the block."""
+    dev = require_gpu()
+    Qs, Ks, Vs, idx = _inputs(7, 1, H, Hkv, Lq, Lk, 0.5)
+    args = [to_device(x, "bf16", dev) for x in (Qs, Ks, Vs)] + [torch.from_numpy(idx).to(dev)]
+    O, O2 = (torch.empty((1, H, Lq, D), dtype=torch.bfloat16, device=dev) for _ in range(2))
+    rmm.rmm_reduced_attention(*args, O)
+    for q0 in range(0, Lq - 16, 16):
+        first = q0 + 16 + Lk - Lq
+        args[1][:, :, first:], args[2][:, :, first::2], args[2][:, :, first + 1::2] = math.nan, math.inf, math.nan
+        rmm.rmm_reduced_attention(*args, O2)
+        rows = slice(q0, q0 + 16)
+        assert torch.equal(O[:, :, rows].contiguous().view(torch.int16), O2[:, :, rows].contiguous().view(torch.int16))
+        for x, y in zip((1, 2), (Ks, Vs)):
+            args[x] = to_device(y, "bf16", dev)
