@@ -42,6 +42,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kTau = 8.f;                // lazy-rescale threshold, log2 units
 constexpr int kBlocks = 512;               // workgroups aimed at (two per CU)
 constexpr int kMinTiles = 4;               // stages per split at least
+constexpr int kFewMaxRows = 256;           // query rows per head taken here at most
 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_le() {
@@ -338,27 +339,49 @@ __global__ __launch_bounds__(256) void attn_few_merge_kernel(const float *__rest
     reinterpret_cast<uint32_t *>(O)[row * (fewk::D / 2) + lane] = pack_bf16x2(v[0], v[1]);
 }
 
-// Ot[bh*D + d][q] and its energies, the queries in order: a thread per dim of
-// one head (Lq % 8 == 0, rows of Ot 16-byte aligned)
-__global__ __launch_bounds__(fewk::D) void attn_few_merge_kmajor_kernel(
+// Ot[bh*D + d][q] and its energies for 16 dims of one head (blockIdx.x): a
+// thread merges one dim of a row at a time, up to 32 rows at once, through LDS into
+// rows of Ot; the energies are added over the queries in a fixed order (Lq % 8 ==
+// 0, Lq <= 256, rows of Ot 16-byte aligned).  32 heads on 8 kv heads x 4000 keys,
+// the whole call in us, 8 / 64 / 256 rows: 17 / 28 / 59 (a thread per dim walking all
+// rows 38 / 163 / 293, the prefill kernel 93 / 94 / 95).
+constexpr int kKmRows = 32, kKmDims = 16;
+__global__ __launch_bounds__(kKmRows *kKmDims) void attn_few_merge_kmajor_kernel(
     const float *__restrict__ part, uint16_t *__restrict__ Ot, int64_t ldot, double *__restrict__ energy, int Lq,
     int S, int64_t rows) {
-    const int64_t bh = blockIdx.x, row_t = bh * fewk::D + threadIdx.x;
-    double e = 0.0;
-    for (int q0 = 0; q0 < Lq; q0 += 8) {
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            float v[1];
-            merge_row(part, rows, bh * Lq + q0 + q, S, static_cast<int>(threadIdx.x), v);
-            const uint32_t x = f32_to_bf16(v[0]);
-            const double y = static_cast<double>(__uint_as_float(x << 16));
-            e = fma(y, y, e);
-            w[q >> 1] = q & 1 ? w[q >> 1] | (x << 16) : x;
-        }
-        *reinterpret_cast<uint4 *>(Ot + row_t * ldot + q0) = make_uint4(w[0], w[1], w[2], w[3]);
+    constexpr int LR = fewk::kFewMaxRows + 8;                  // staged dim row (16-byte aligned)
+    __shared__ __attribute__((aligned(16))) uint16_t val[kKmDims][LR];
+    __shared__ double en[kKmDims][fewk::kFewMaxRows / 8];
+    const int tid = threadIdx.x, nt = blockDim.x, d0 = kKmDims * static_cast<int>(blockIdx.x);
+    const int64_t bh = blockIdx.y;
+    for (int q = tid / kKmDims; q < Lq; q += nt / kKmDims) {
+        float v[1];
+        merge_row(part, rows, bh * Lq + q, S, d0 + tid % kKmDims, v);
+        val[tid % kKmDims][q] = f32_to_bf16(v[0]);
     }
-    energy[row_t] = e;
+    __syncthreads();
+    const int nq = Lq / 8;
+    for (int i = tid; i < kKmDims * nq; i += nt) {
+        const int d = i / nq, c = i % nq;
+        const uint4 x = *reinterpret_cast<const uint4 *>(&val[d][8 * c]);
+        *reinterpret_cast<uint4 *>(Ot + (bh * fewk::D + d0 + d) * ldot + 8 * c) = x;
+        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+        double e = 0.0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double y0 = static_cast<double>(__uint_as_float(w[j] << 16));
+            const double y1 = static_cast<double>(__uint_as_float(w[j] & 0xffff0000u));
+            e = fma(y0, y0, e);
+            e = fma(y1, y1, e);
+        }
+        en[d][c] = e;
+    }
+    __syncthreads();
+    if (tid < kKmDims) {
+        double e = 0.0;
+        for (int c = 0; c < nq; ++c) e += en[tid][c];
+        energy[bh * fewk::D + d0 + tid] = e;
+    }
 }
 
 }  // namespace
@@ -417,7 +440,7 @@ hipError_t launch_splits(const uint16_t *Q, const uint16_t *Kc, const uint16_t *
 // x 32 heads x 64 rows, 256 blocks, 80 against 101; 128 rows, 512 blocks, 144
 // against 102; 4 x 32 heads on 8 kv heads x 128 rows, 256 blocks, 69 against 116).
 bool attn_few_ok(int64_t batch, int64_t H, int64_t Hkv, int64_t Lq, int64_t Lk, int64_t k) {
-    if (Lq > 256 || Lk * attn_k_steps(k) * 32 < Lq * (fewk::D + 2) * static_cast<int64_t>(sizeof(float))) return false;
+    if (Lq > fewk::kFewMaxRows || Lk * attn_k_steps(k) * 32 < Lq * (fewk::D + 2) * static_cast<int64_t>(sizeof(float))) return false;
     if (Lq <= fewk::TQ) return true;
     const int64_t grp = H / Hkv, chunk = head_chunk(grp);
     const int64_t blocks = batch * Hkv * ((grp + chunk - 1) / chunk) * ((Lq + fewk::TQ - 1) / fewk::TQ);
@@ -445,8 +468,8 @@ hipError_t launch_attn_few_kmajor_bf16(const uint16_t *Q, const uint16_t *Kc, co
     float *part = static_cast<float *>(workspace);
     const hipError_t e = launch_splits(Q, Kc, V, idx, batch, H, Hkv, Lq, Lk, k, scale, causal, nullptr, part, &S, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_few_merge_kmajor_kernel, dim3(static_cast<unsigned>(batch * H)), dim3(fewk::D), 0, stream,
-                       part, Ot, ldot, energy, static_cast<int>(Lq), S, batch * H * Lq);
+    hipLaunchKernelGGL(attn_few_merge_kmajor_kernel, dim3(fewk::D / kKmDims, static_cast<unsigned>(batch * H)),
+                       dim3(kKmDims * static_cast<unsigned>(Lq < kKmRows ? Lq : kKmRows)), 0, stream, part, Ot, ldot, energy, static_cast<int>(Lq), S, batch * H * Lq);
     return hipGetLastError();
 }
 
