@@ -636,10 +636,9 @@ bool qk_rows_ok(int64_t Lk, int64_t D, const void *S) {
 namespace {
 // rows of S on 128-byte lines
 bool qk_lines(int64_t Lk, const void *S) { return Lk % 64 == 0 && reinterpret_cast<uintptr_t>(S) % 128 == 0; }
-// Gathered dims (half the matrix work) pay only for long rows, where the masked
-// product no longer hides behind the stores: 32 heads, k = 64, us masked / gathered:
-// 4096 keys 232 / 249, 8192 841 / 792, without the mask 850 / 813 (8 heads x 8192:
-// 242 / 202).
+// Gathered dims (half the matrix work) where the masked product no longer hides
+// behind the stores: 32 heads, k = 64, us masked / gathered: 8192 keys 841 / 792,
+// without the mask 850 / 813 (8 heads x 8192: 242 / 202).
 bool qk_gathered(int64_t base, int64_t Lk, int64_t D, int64_t k, const void *S) {
     return D == 128 && k <= 64 && Lk >= 6144 && base >= 256 && qk_lines(Lk, S);
 }
@@ -652,11 +651,18 @@ hipError_t launch_qk_rowstats_bf16(const uint16_t *Q, const uint16_t *Kc, const 
     if (!qk_rows_ok(Lk, D, S)) return hipErrorNotSupported;
     const int64_t qb = (Lq + rowk::BQ - 1) / rowk::BQ;
     dim3 grid(static_cast<unsigned>(qb), static_cast<unsigned>(batch * H));
-    // a block owns its rows' statistics: one share of the keys
+    // A block owns its rows' statistics: one share of the keys.  Two blocks of
+    // 128-key tiles per CU where there are blocks for it and for the shortest rows;
+    // else 256-key tiles, with gathered dims where few are kept (us at D = 128, 128-key /
+    // 256-key / gathered tiles: 4 x 28 heads x 384, k = 103 20 / 31; 1 x 32 x 2048, k = 64
+    // 80 / 90 / 90; 1 x 32 x 3776, k = 103 229 / 271; 1 x 8 x 3072, k = 32 74 / 60 / 55).
+    const int64_t base = qb * batch * H;
+    const bool narrow = D == 64 || Lk <= 400 || (base > 256 && Lk < 4608 && (Lk < 2560 || base >= 800));
     auto kern = D == 64 ? qk_bf16_rows_kernel<64, 1, 256, 128, true>
-              : qk_gathered(qb * batch * H, Lk, D, k, S) ? qk_bf16_rows_kernel<128, 1, 512, 256, true, 0, true>
-                                                         : qk_bf16_rows_kernel<128, 2, 512, 256, true>;
-    hipLaunchKernelGGL(kern, grid, dim3(D == 128 ? 512 : 256), 0, stream, Q, Kc, idx, S,
+              : narrow ? qk_bf16_rows_kernel<128, 2, 256, 128, true>
+              : k <= 48 || qk_gathered(base, Lk, D, k, S) ? qk_bf16_rows_kernel<128, 1, 512, 256, true, 0, true>
+                                                          : qk_bf16_rows_kernel<128, 2, 512, 256, true>;
+    hipLaunchKernelGGL(kern, grid, dim3(narrow ? 256 : 512), 0, stream, Q, Kc, idx, S,
                        static_cast<int>(H), static_cast<int>(Hkv), static_cast<int>(Lq),
                        static_cast<int>(Lk), static_cast<int>(k), scale, causal ? 1 : 0, 1, rmax, rinv);
     return hipGetLastError();
@@ -668,21 +674,58 @@ hipError_t launch_qk_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *
                           hipStream_t stream) {
     // 32-bit byte offsets into a block's 128 rows of S
     if ((D == 64 || D == 128) && Lk <= (1 << 22)) {
-        // Blocks of 128-key tiles (two per CU) whose keys are split C ways up to
-        // 512 blocks, and in two for long rows on whole lines; us, D = 128:
-        //   1 x 32 heads x 1001 keys, k = 103: C = 1 / 2 / 4 22.6 / 19.0 / 22.2
-        //   1 x 32 x 2048, k = 64: C = 1 / 2 58 / 64;  1 x 40 x 2048: 93 / 78
-        //   1 x 32 x 4096, k = 64: C = 1 / 2 / 4 258 / 232 / 240
-        // 256-key tiles (one block per CU, 512-byte row pieces) for the longest rows
-        // (8192 keys, k = 128: 802 against 838) and where pieces are shifted to
-        // lines, from 1408 keys on (1 x 32 x 3000: 173 against 242 unshifted; 2 x 32 x
-        // 1001: 49 against 33; 2 x 32 x 1501: 94 against 106).
+        // Which form (us at D = 128 unless said; the others in brackets).
         const int64_t qb = (Lq + rowk::BQ - 1) / rowk::BQ, base = qb * batch * H;
-        const bool lines = qk_lines(Lk, S), gathered = qk_gathered(base, Lk, D, k, S);
-        const bool shift = !lines && Lk >= 1408 && base >= 512;
-        const bool wide = D == 128 && (shift || (lines && Lk >= 6144 && base >= 256));
+        const bool lines = qk_lines(Lk, S), rows16 = qk_rows_ok(Lk, D, S);
+        const bool square = 2 * Lq > Lk, half = causal && square;   // half: about half the tiles have a product
+        // Long rows that share lines, once S is past the 256 MB that the memory side
+        // cache absorbs: pieces shifted to lines, unless every other row starts at half
+        // a line.  1 x 28 heads x 2712 keys, k = 64 121 [128-key tiles 159, gathered 154],
+        // 1 x 64 x 2001 (odd) 177 [208], 4 x 32 x 1416 163 [206]; at 257 MB, 1 x 64 x 1416
+        // 80 [gathered 72]; 1 x 28 x 4000 (half lines) 252 [gathered 243].
+        const bool past = !lines && Lk >= 1408 && 2 * batch * H * Lq * Lk >= 320000000;
+        const bool shift = past && (D == 64 || !(Lk % 32 == 0 && reinterpret_cast<uintptr_t>(S) % 64 == 0));
+        // Gathered dims (half the matrix work at k = 64), with 256-key tiles, one block
+        // per CU: for the longest rows and the half-line ones above; causal from 4096 keys
+        // on (1 x 32 heads x 4096, k = 32: 218 [237]); without the mask from 1280 keys on
+        // if few dims are kept or rows share lines (1 x 64 x 4096, k = 32: 386 [436]; 1 x 8 x
+        // 3584 40 [43]; k = 64: 445 [447]).
+        const bool gathered = D == 128 && k <= 64 && rows16 && !shift &&
+            (qk_gathered(base, Lk, D, k, S) || past ||
+             (half ? (base >= 512 && Lk >= 4096) || (k <= 48 && base >= 1024 && Lk >= 1000 && Lk < 1280)
+                   : square && (k <= 48 || !lines) && ((base >= 512 && Lk >= 1280) || (base >= 160 && Lk >= 2000))));
+        // 256-key tiles (512-byte row pieces) otherwise for the longest rows (8192 keys,
+        // k = 128: 802 [838]) and wherever S is past the cache off the lines
+        const bool wide = D == 128 && (gathered || past || (lines && Lk >= 6144 && base >= 256));
         const int64_t tiles = (Lk + (wide ? 255 : 127)) / (wide ? 256 : 128);
-        int64_t C = wide || shift ? 1 : base < 512 ? (512 + base - 1) / base : lines && base > 512 && Lk >= 2048 ? 2 : 1;
+        // Shares of the keys, two blocks of 128-key tiles per CU.  Causal rows of middle
+        // length: three, which start and end at different times (1 x 64 x 1536, k = 64 66
+        // [1: 77, 2: 76], 4 x 32 x 2240 258 [284, 301], 1 x 16 x 3000 77 [99, 90], 64 dims 1 x
+        // 28 x 1411 25 [33, 30]; at 4096 keys 242 [244, 238]).  Otherwise, below 160 blocks,
+        // as many as give 512; up to there the count with the fewest tiles in all rounds (1 x
+        // 28 heads x 1000 keys, 224 blocks: 2 shares 15.6 [1: 20.0, 3: 19.0]; 4 x 32 x 384, 384
+        // blocks: 1 share 13.2 [2: 17.8]), two rather than one where that costs little (1 x
+        // 16 x 2240, 288 blocks: 42 [52]).  Long rows on lines: two (4096 keys, k = 128, no
+        // mask).
+        const bool three = half && Lk >= 1280 && Lk < 3968 &&
+            (base > 512 || (base < 512 && base >= 171 && (tiles >= 20 || (D == 64 && tiles >= 11 && (base <= 200 || base >= 270)))));
+        int64_t C = 1;
+        if (wide || shift) {
+            C = 1;
+        } else if (three) {
+            C = 3;
+        } else if (base < 160) {
+            C = (512 + base - 1) / base;
+        } else if (base < 512) {
+            int64_t least = tiles;
+            const bool two = base <= 352 || (tiles >= 18 && base <= 448);
+            for (int64_t c = 2; c <= (512 + base - 1) / base; ++c) {
+                const int64_t t = (base * c + 511) / 512 * ((tiles + c - 1) / c);
+                if (t < least || (c == 2 && two && t <= least + (tiles >= 9))) { least = t; C = c; }
+            }
+        } else if (lines && base > 512 && Lk >= 2048 && (D == 128 || half || Lk < 4096)) {
+            C = 2;
+        }
         if (C > tiles) C = tiles;
         const int64_t tpc = (tiles + C - 1) / C;
         C = (tiles + tpc - 1) / tpc;                      // no empty share
@@ -697,7 +740,7 @@ hipError_t launch_qk_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *
         if (gathered) return run(qk_bf16_rows_kernel<128, 1, 512, 256, false, 0, true>);
         if (shift) return wide ? run(qk_bf16_rows_kernel<128, 2, 512, 256, false, 2>) : run(qk_bf16_rows_kernel<64, 1, 256, 128, false, 2>);
         if (wide) return run(qk_bf16_rows_kernel<128, 2, 512, 256>);
-        if (qk_rows_ok(Lk, D, S)) return D == 64 ? run(qk_bf16_rows_kernel<64, 1, 256, 128>) : run(qk_bf16_rows_kernel<128, 2, 256, 128>);
+        if (rows16) return D == 64 ? run(qk_bf16_rows_kernel<64, 1, 256, 128>) : run(qk_bf16_rows_kernel<128, 2, 256, 128>);
         return D == 64 ? run(qk_bf16_rows_kernel<64, 1, 256, 128, false, 1>) : run(qk_bf16_rows_kernel<128, 2, 256, 128, false, 1>);
     }
     constexpr int BM = 128, BN = 128, BK = 32, WM = 2, WN = 2;

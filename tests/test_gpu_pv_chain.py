@@ -245,6 +245,9 @@ def _integer_qk(seed, batch, H, Hkv, Lq, Lk, D, k):
     (2, 2, 1, 130, 392, 128, 128, False, 3),    # no mask, Lk not a multiple of the key tile
     (1, 2, 1, 1024, 1024, 128, 64, True, 4),    # several key tiles per row
     (1, 1, 1, 8, 8, 64, 1, True, 5),            # one partial tile, k = 1
+    (1, 90, 2, 300, 408, 128, 100, True, 6),    # more than 256 blocks: 128-key tiles
+    (1, 2, 1, 260, 520, 128, 33, True, 7),      # few blocks: 256-key tiles, gathered dims
+    (1, 2, 1, 260, 520, 128, 100, True, 8),     # ... masked dims
 ])
 def test_qk_rowstats_chain(batch, H, Hkv, Lq, Lk, D, k, causal, seed):
     dev = require_gpu()
@@ -265,7 +268,7 @@ def test_qk_rowstats_chain(batch, H, Hkv, Lq, Lk, D, k, causal, seed):
     S2 = torch.empty_like(S)
     rmm.rmm_reduced_qk(Qd, Kd, idx_d, S2, causal=causal)
     assert torch.equal(S2.view(torch.int16), S.view(torch.int16))
-    BT = 128 if (D == 64 or k > 96) else 256
+    BT = 128 if D == 64 else 256                 # the widest key tile: at most BT / 8 lanes per row
     check_row_stats(rmax.cpu().numpy(), rinv.cpu().numpy(),
                     wl.decode(ref, "bf16").astype(np.float64).reshape(U * Lq, Lk), BT // 8)
     Vbits = wl.random_case(seed + 7, (batch, Hkv, Lk, D), "bf16")
@@ -304,7 +307,7 @@ def test_layer_8b_qk_rowstats(r):
     assert np.all(n_inf == a.L * (a.L - 1) // 2)
     sel = (np.arange(a.H)[:, None] * a.L + rows[None, :]).reshape(-1)
     Sref = wl.decode(ref, "bf16").astype(np.float64).reshape(-1, a.L)
-    BT = 128 if k > 96 else 256
+    BT = 256                                     # the widest key tile: at most BT / 8 lanes per row
     check_row_stats(rmax.cpu().numpy()[sel], rinv.cpu().numpy()[sel], Sref, BT // 8)
     # the weights from these statistics on the sampled rows of every head
     Pt = torch.empty((1, a.H, a.L, a.L), dtype=torch.bfloat16, device=dev)

@@ -1,6 +1,6 @@
 """The row-streaming reduced QK^T at the edges of its forms (shares of the keys,
 rows of S on any element, pieces shifted to lines, gathered dims) against
-float64 products: odd lengths, misaligned S, Lq != Lk, guards around S."""
+float64 products: odd lengths, misaligned S, Q and K, Lq != Lk, guards around S."""
 import math
 
 import numpy as np
@@ -15,17 +15,23 @@ pytestmark = gpu
 
 
 def _run(seed, batch, H, Hkv, Lq, Lk, D, k, causal, shift):
-    """S written `shift` elements into a guarded buffer; a sample of heads is checked."""
+    """S written `shift` elements into a guarded buffer, Q and K read `shift` and 2 * `shift`
+    elements past a 16-byte boundary; a sample of heads is checked."""
     dev = require_gpu()
     Qs = wl.encode(wl.heavy_tailed_heads((seed, 700), batch * H, Lq, D), "bf16").reshape(batch, H, Lq, D)
     Ks = wl.encode(wl.heavy_tailed_heads((seed, 701), batch * Hkv, Lk, D), "bf16").reshape(batch, Hkv, Lk, D)
     rng = np.random.default_rng(seed)
     idx = np.sort(np.stack([rng.choice(D, k, replace=False) for _ in range(batch * H)]), axis=1).astype(np.int32)
     n = batch * H * Lq * Lk
+    qk_in = []
+    for i, x in enumerate((Qs, Ks)):                    # off 16-byte boundaries with S
+        b = torch.empty(x.size + 8, dtype=torch.bfloat16, device=dev)
+        off = (shift * (i + 1)) % 8
+        qk_in.append(b[off:off + x.size].view(x.shape))
+        qk_in[i].copy_(to_device(x, "bf16", dev))
     buf = torch.full((n + 128,), 7.0, dtype=torch.bfloat16, device=dev)
     S = buf[64 + shift:64 + shift + n].view(batch, H, Lq, Lk)
-    rmm.rmm_reduced_qk(to_device(Qs, "bf16", dev), to_device(Ks, "bf16", dev),
-                       torch.from_numpy(idx).to(dev).view(batch, H, k), S, causal=causal)
+    rmm.rmm_reduced_qk(*qk_in, torch.from_numpy(idx).to(dev).view(batch, H, k), S, causal=causal)
     assert bool((buf[:64 + shift] == 7.0).all()) and bool((buf[64 + shift + n:] == 7.0).all())
     scale = 1 / math.sqrt(D)
     drop = np.arange(Lk)[None, :] > np.arange(Lq)[:, None] + (Lk - Lq)
@@ -52,11 +58,21 @@ def _run(seed, batch, H, Hkv, Lq, Lk, D, k, causal, shift):
     (1, 2, 1, 300, 517, 64, 32, False, 0),      # 64 dims, several shares
     (1, 3, 1, 257, 640, 128, 128, True, 0),     # rows on lines, all dims
     (1, 4, 4, 513, 1032, 128, 1, True, 0),      # 16-byte rows, the last share short
-    (2, 130, 2, 200, 1411, 128, 90, True, 0),   # pieces shifted to lines, odd rows
-    (1, 512, 4, 7, 1410, 128, 40, False, 5),    # ... every misalignment of even rows, Lk - Lq large
+    (2, 130, 2, 200, 1411, 128, 90, True, 0),   # long odd rows, below the size at which pieces are shifted
+    (1, 512, 4, 7, 1410, 128, 40, False, 5),    # ... even rows on odd addresses, Lk - Lq large
     (1, 300, 2, 129, 1416, 128, 70, True, 0),   # ... 16-byte rows
     (1, 512, 8, 40, 1539, 64, 20, True, 1),     # ... 64 dims
-    (1, 1024, 8, 5, 6144, 128, 33, True, 0),    # gathered dims
+    (1, 1024, 8, 5, 6144, 128, 33, True, 0),    # gathered dims: the longest rows
+    (1, 260, 4, 303, 2053, 128, 90, True, 0),   # 320 MB and more: pieces shifted to lines, odd rows
+    (1, 256, 4, 322, 2042, 128, 40, False, 5),  # ... every misalignment of even rows
+    (1, 250, 2, 316, 2056, 128, 128, True, 0),  # ... 16-byte rows
+    (1, 280, 8, 290, 2003, 64, 20, True, 1),    # ... 64 dims
+    (1, 256, 4, 304, 2080, 128, 100, True, 0),  # ... every other row at half a line: 256-key tiles
+    (1, 256, 4, 304, 2080, 128, 50, False, 0),  # ... gathered
+    (1, 48, 2, 1416, 1416, 128, 17, False, 0),  # gathered without the mask
+    (2, 60, 4, 1010, 1016, 128, 48, True, 0),   # ... and with it, many blocks
+    (1, 48, 8, 1288, 1288, 128, 70, True, 0),   # three shares of the keys, causal
+    (1, 23, 23, 300, 900, 64, 64, False, 0),    # one block short of two rounds, 64 dims
 ])
 def test_qk_rows(batch, H, Hkv, Lq, Lk, D, k, causal, shift):
     _run(Lq + Lk, batch, H, Hkv, Lq, Lk, D, k, causal, shift)
