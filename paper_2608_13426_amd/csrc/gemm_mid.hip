@@ -270,58 +270,80 @@ __global__ __launch_bounds__(WM *WN * 64, WM *WN / 4) void gemm_kmajor_mid_kerne
     const int lr = lane & 31, lh = lane >> 5;
     uint16_t *Yt = Y + (static_cast<int64_t>(unit) * M + m0) * ldy;
     const int rows = min(BM, M - m0);
-    const bool full_n = n0 + BN <= N;
-    auto store = [&](int j, int i, int gq, float v0, float v1, float v2, float v3) {
-        const int ml = wm * TM + 32 * i + lr;
-        const int n = n0 + wn * TN + 32 * j + 8 * gq + 4 * lh;
-        if (ml >= rows) return;
-        const uint32_t w0 = pack_bf16x2(v0, v1), w1 = pack_bf16x2(v2, v3);
-        uint16_t *p = Yt + ml * ldy + n;
-        if (vec_y && full_n) {
-            *reinterpret_cast<uint2 *>(p) = make_uint2(w0, w1);
-        } else {
-            const uint16_t e[4] = {static_cast<uint16_t>(w0), static_cast<uint16_t>(w0 >> 16),
-                                   static_cast<uint16_t>(w1), static_cast<uint16_t>(w1 >> 16)};
+    if constexpr (BM == 64) {
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr)
-                if (n + rr < N) p[rr] = e[rr];
-        }
-    };
-    if constexpr (BM == 128 && BN == 128 && S == 4 && ASZ == 8192) {
-        if (vec_y == 2 && full_n) {
-            // through the idle ring, 32 rows per X slot, so that 16 lanes write
-            // a whole 256-byte row piece; 16-byte chunk c of a row at c ^ (row % 16)
-            auto obj = [&](int q) -> char * { return q == 0 ? sA0 : q == 1 ? sA1 : q == 2 ? sA2 : sA3; };
-            __syncthreads();
+        for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+                for (int gq = 0; gq < 4; ++gq) {
+                    const int ml = wm * TM + 32 * i + lr;
+                    const int n = n0 + wn * TN + 32 * j + 8 * gq + 4 * lh;
+                    if (ml >= rows) continue;
+                    const uint32_t w0 = pack_bf16x2(acc[j][i][4 * gq], acc[j][i][4 * gq + 1]);
+                    const uint32_t w1 = pack_bf16x2(acc[j][i][4 * gq + 2], acc[j][i][4 * gq + 3]);
+                    uint16_t *p = Yt + ml * ldy + n;
+                    if (vec_y && n + 4 <= N) {
+                        *reinterpret_cast<uint2 *>(p) = make_uint2(w0, w1);
+                    } else {
+                        const uint16_t e[4] = {static_cast<uint16_t>(w0), static_cast<uint16_t>(w0 >> 16),
+                                               static_cast<uint16_t>(w1), static_cast<uint16_t>(w1 >> 16)};
 #pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        const int c = (wn * TN) / 8 + 4 * j + gq;
-                        *reinterpret_cast<uint2 *>(obj(wm * FM + i) + lr * RB + 16 * (c ^ (lr & 15)) + 8 * lh) =
-                            make_uint2(pack_bf16x2(acc[j][i][4 * gq], acc[j][i][4 * gq + 1]),
-                                       pack_bf16x2(acc[j][i][4 * gq + 2], acc[j][i][4 * gq + 3]));
+                        for (int rr = 0; rr < 4; ++rr)
+                            if (n + rr < N) p[rr] = e[rr];
                     }
-            __syncthreads();
-            const int r32 = tid >> 4, c = tid & 15;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(obj(q) + r32 * RB + 16 * (c ^ (r32 & 15)));
-                if (32 * q + r32 < rows)
-                    *reinterpret_cast<uint4 *>(Yt + (32 * q + r32) * ldy + n0 + 8 * c) = v;
-            }
-            return;
-        }
+                }
+        return;
     }
+    // Through the idle ring, so that neighbouring lanes write neighbouring
+    // pieces of a row (16, 8 or 2 bytes, as Y's rows are aligned; where the tile
+    // is cut by N too): OR rows per X slot, 16-byte chunk c of a row at c ^ (row %
+    // CH).  Against pieces of four elements straight from the accumulators (us): 5820
+    // x 72 -> 352, k = 36 9.4 -> 5.4, 602 x 72 -> 3565 (odd) 11.2 -> 6.9, 2536 x 1024 -> 1864
+    // in rows of 1867, k = 768 30 -> 19.
+    constexpr int CH = BN / 8, OR = ASZ / RB;
+    static_assert(BM == 64 || (OR % 32 == 0 && BM == S * OR), "staged output");
+    auto obj = [&](int r) -> char * {
+        const int q = r / OR;
+        return (q == 0 ? sA0 : q == 1 ? sA1 : q == 2 ? sA2 : sA3) + (r % OR) * RB;
+    };
+    __syncthreads();                                     // every wave's last reads and loads are done
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int gq = 0; gq < 4; ++gq)
-                store(j, i, gq, acc[j][i][4 * gq], acc[j][i][4 * gq + 1], acc[j][i][4 * gq + 2], acc[j][i][4 * gq + 3]);
+            for (int gq = 0; gq < 4; ++gq) {
+                const int r = wm * TM + 32 * i + lr, c = (wn * TN) / 8 + 4 * j + gq;
+                *reinterpret_cast<uint2 *>(obj(r) + 16 * (c ^ (r % CH)) + 8 * lh) =
+                    make_uint2(pack_bf16x2(acc[j][i][4 * gq], acc[j][i][4 * gq + 1]),
+                               pack_bf16x2(acc[j][i][4 * gq + 2], acc[j][i][4 * gq + 3]));
+            }
+    __syncthreads();
+    // elements n .. n + U - 1 of row r, per thread
+    auto out = [&](auto Uv) {
+        constexpr int U = decltype(Uv)::value, LPR = BN / U, RPP = NT / LPR;
+        const int u = tid % LPR, n = n0 + U * u;
+#pragma unroll
+        for (int p = 0; p < BM / RPP; ++p) {
+            const int r = RPP * p + tid / LPR;
+            if (r >= rows) continue;
+            const char *src = obj(r) + 16 * ((U * u / 8) ^ (r % CH)) + 2 * (U * u % 8);
+            uint16_t *dst = Yt + r * ldy + n;
+            if (n + U <= N) {
+                if constexpr (U == 8) *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(src);
+                else if constexpr (U == 4) *reinterpret_cast<uint2 *>(dst) = *reinterpret_cast<const uint2 *>(src);
+                else *dst = *reinterpret_cast<const uint16_t *>(src);
+            } else if constexpr (U > 1) {
+#pragma unroll
+                for (int e = 0; e < U - 1; ++e)
+                    if (n + e < N) dst[e] = reinterpret_cast<const uint16_t *>(src)[e];
+            }
+        }
+    };
+    if (vec_y == 2) out(std::integral_constant<int, 8>{});
+    else if (vec_y == 1) out(std::integral_constant<int, 4>{});
+    else out(std::integral_constant<int, 1>{});
 }
 
 template <int BM, int BN, int WM, int WN, int BKS, int S>

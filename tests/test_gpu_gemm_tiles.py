@@ -21,6 +21,8 @@ pytestmark = gpu
     (1, 1100, 160, 1040, 97, 0),    # 128 x 128 tiles: staged and partial columns
     (1, 1025, 160, 1023, 160, 4),   # ... odd Y rows
     (2, 700, 3800, 1152, 3700, 4),  # ... two units, two segments, 8-byte Y rows
+    (1, 1100, 72, 1139, 40, 1),     # ... 8-byte rows, a last tile of 115 columns
+    (2, 1030, 72, 523, 33, 3),      # ... odd columns and rows
     (1, 3000, 72, 3072, 40, 0),     # 256 x 256 tiles (144 of them)
     (1, 130, 72, 128, 33, 1 << 23), # Y rows too long for 32-bit offsets
 ])
@@ -44,6 +46,33 @@ def test_kmajor_tiles(B, M, K, N, k, pad):
         check_product(got[b], A @ W[idx[b]], np.abs(A) @ np.abs(W[idx[b]]), k, "bf16")
     tail = Y[:, :, N:N + 64]
     assert bool((tail == 7.0).all())                       # nothing past N written
+
+
+@pytest.mark.parametrize("B,M,N,k,pad", [
+    (350, 300, 128, 33, 0),         # 1050 blocks of 128 rows: 256 x 128 tiles, partial in m
+    (350, 300, 64, 70, 4),          # ... half the columns, 8-byte rows
+    (350, 290, 72, 9, 5),           # ... odd rows: element stores
+    (520, 257, 5, 64, 0),           # ... one row past a tile, few columns
+])
+def test_kmajor_tall_tiles(B, M, N, k, pad):
+    """Many units of narrow products (value products): partial tiles both ways, guarded columns."""
+    dev = require_gpu()
+    g = torch.Generator(device=dev).manual_seed(B + N)
+    K, ld = 80, (M + 7) // 8 * 8
+    xt = torch.full((B, K, ld), float("nan"), dtype=torch.bfloat16, device=dev)    # NaN past M
+    xt[:, :, :M] = torch.randn(B, K, M, device=dev, generator=g).bfloat16()
+    W = torch.randn(K, (N + 7) // 8 * 8, device=dev, generator=g).bfloat16()
+    idx = torch.stack([torch.sort(torch.randperm(K, device=dev, generator=g)[:k]).values for _ in range(B)])
+    Y = torch.full((B, M, N + pad), 7.0, dtype=torch.bfloat16, device=dev)
+    rmm.rmm_reduced_gemm_kmajor(xt[:, :, :M], W[:, :N], idx.int().contiguous(), Y[:, :, :N])
+    assert bool((Y[:, :, N:] == 7.0).all())
+    for b in range(0, B, 7):
+        A, Wb = xt[b, idx[b], :M].double().t().cpu().numpy(), W[idx[b], :N].double().cpu().numpy()
+        check_product(from_device(Y[b, :, :N]), A @ Wb, np.abs(A) @ np.abs(Wb), k, "bf16")
+    for b in range(B):                                     # every unit within a bf16 rounding of a 32-bit product
+        ref = xt[b, idx[b], :M].float().t() @ W[idx[b], :N].float()
+        assert bool(torch.isfinite(Y[b, :, :N]).all())
+        assert float((Y[b, :, :N].float() - ref).abs().max()) <= 2.0 ** -7 * float(ref.abs().max())
 
 
 @pytest.mark.parametrize("H,Hkv,Lq,Lk,kt", [(2, 1, 1, 40, 33), (4, 2, 129, 129, 60), (2, 2, 300, 420, 200),
