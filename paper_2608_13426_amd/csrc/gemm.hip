@@ -829,13 +829,15 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_kmajor_tr_kernel(
 // transposed in registers.  Tails of the list are zeros; rows past M and
 // columns past N are loaded clamped and never stored.  Bound by the length of
 // the list's dependent tiles at small sizes and by LDS reads at large ones.
+// Rows of Y off 16-byte boundaries: the operands change places, so that 16 lanes
+// write 16 neighbouring elements (4 units of 703 x 42 -> 518, k = 11: 8.0 -> 6.1 us).
 // Against the 64 x 64 VALU tile it replaces (us): 128 x 512 -> 512 at k = 256
 // 46.3 -> 11.2 (launch included; 7.1 alone), 1024^3 at k = 512 131 -> 25, 4096^3
 // at k = 2048 1433 -> 908 (76 of about 150 TFLOP/s); the same error.
-template <int BM, int BN, int BK, bool VECW>
+template <int BM, int BN, int BK, bool VECW, bool VECY>
 __global__ __launch_bounds__(256) void gemm_gather_f32_kernel(
     const float *__restrict__ X, const float *__restrict__ W, const int32_t *__restrict__ idx,
-    float *__restrict__ Y, int M, int N, int k, int64_t ldx, int64_t ldw, int64_t ldy, int vec_y) {
+    float *__restrict__ Y, int M, int N, int k, int64_t ldx, int64_t ldw, int64_t ldy) {
     constexpr int LS = BK + 4;                       // floats per LDS row
     constexpr int FM = BM / 32, FN = BN / 32;        // 16 x 16 fragments per wave
     constexpr int RPP = 256 / BK, XR = BM / RPP;     // X rows per pass and per thread
@@ -922,12 +924,29 @@ __global__ __launch_bounds__(256) void gemm_gather_f32_kernel(
                 for (int j = 0; j < FN; ++j)
 #pragma unroll
                     for (int i = 0; i < FM; ++i)
-                        acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][e], a[i][e], acc[j][i], 0, 0, 0);
+                        acc[j][i] = VECY ? __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][e], a[i][e], acc[j][i], 0, 0, 0)
+                                         : __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[j][i], 0, 0, 0);
         }
         if (t0 + BK < k) stash(buf ^ 1);
         __syncthreads();
     }
-    // acc[j][i][r]: n = n0 + wnb + 16j + 4*(lane/16) + r, m = m0 + wm + 16i + lane%16
+    // VECY: acc[j][i][r] is n = n0 + wnb + 16j + 4*(lane/16) + r, m = m0 + wm + 16i +
+    // lane%16; else m = m0 + wm + 16i + 4*(lane/16) + r, n = n0 + wnb + 16j + lane%16
+    if constexpr (!VECY) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = m0 + wm + 16 * i + 4 * lg + r;
+                if (m >= M) continue;
+#pragma unroll
+                for (int j = 0; j < FN; ++j) {
+                    const int n = n0 + wnb + 16 * j + lr;
+                    if (n < N) Y[static_cast<int64_t>(m) * ldy + n] = acc[j][i][r];
+                }
+            }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
         const int m = m0 + wm + 16 * i + lr;
@@ -936,7 +955,7 @@ __global__ __launch_bounds__(256) void gemm_gather_f32_kernel(
         for (int j = 0; j < FN; ++j) {
             const int n = n0 + wnb + 16 * j + 4 * lg;
             float *p = Y + static_cast<int64_t>(m) * ldy + n;
-            if (vec_y && n + 4 <= N) {
+            if (n + 4 <= N) {
                 *reinterpret_cast<f32x4_t *>(p) = acc[j][i];
             } else {
 #pragma unroll
@@ -1085,7 +1104,7 @@ hipError_t launch_gemm_f32(const float *X, const float *W, const int32_t *idx, i
                            float *Y, int64_t ldy, hipStream_t stream) {
     (void)K;
     const bool vec = reinterpret_cast<uintptr_t>(W) % 16 == 0 && ldw % 4 == 0;
-    const int vec_y = reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 4 == 0;
+    const bool vec_y = reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 4 == 0;
     // 64 x 64 tiles once they give every CU one, 32 x 32 (a quarter of the work
     // per workgroup) below
     const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64) * B;
@@ -1094,11 +1113,18 @@ hipError_t launch_gemm_f32(const float *X, const float *W, const int32_t *idx, i
         dim3 grid(static_cast<unsigned>((N + t - 1) / t), static_cast<unsigned>((M + t - 1) / t),
                   static_cast<unsigned>(B));
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, X, W, idx, Y, static_cast<int>(M),
-                           static_cast<int>(N), static_cast<int>(k), ldx, ldw, ldy, vec_y);
+                           static_cast<int>(N), static_cast<int>(k), ldx, ldw, ldy);
         return hipGetLastError();
     };
-    if (t == 64) return vec ? launch(gemm_gather_f32_kernel<64, 64, 32, true>) : launch(gemm_gather_f32_kernel<64, 64, 32, false>);
-    return vec ? launch(gemm_gather_f32_kernel<32, 32, 64, true>) : launch(gemm_gather_f32_kernel<32, 32, 64, false>);
+    if (t == 64)
+        return vec ? (vec_y ? launch(gemm_gather_f32_kernel<64, 64, 32, true, true>)
+                            : launch(gemm_gather_f32_kernel<64, 64, 32, true, false>))
+                   : (vec_y ? launch(gemm_gather_f32_kernel<64, 64, 32, false, true>)
+                            : launch(gemm_gather_f32_kernel<64, 64, 32, false, false>));
+    return vec ? (vec_y ? launch(gemm_gather_f32_kernel<32, 32, 64, true, true>)
+                        : launch(gemm_gather_f32_kernel<32, 32, 64, true, false>))
+               : (vec_y ? launch(gemm_gather_f32_kernel<32, 32, 64, false, true>)
+                        : launch(gemm_gather_f32_kernel<32, 32, 64, false, false>));
 }
 
 }  // namespace rmm

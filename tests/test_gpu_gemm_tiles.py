@@ -107,6 +107,7 @@ def test_pv_kmajor_causal_trim(H, Hkv, Lq, Lk, kt):
     (1, 40, 130, 64, 128, 4),       # whole list tiles
     (1, 1025, 96, 1030, 31, 2),     # 64 x 64 tiles: list shorter than a tile, 8-byte rows
     (3, 600, 100, 640, 97, 0),      # ... several units
+    (1, 1025, 96, 1029, 31, 3),     # ... 16-byte rows of Y, cut by N
 ])
 def test_f32_tiles(B, M, K, N, k, wpad):
     dev = require_gpu()
