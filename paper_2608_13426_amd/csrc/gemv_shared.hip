@@ -259,8 +259,9 @@ __device__ __forceinline__ void share_steps(F &&f, int st, int nst, std::integer
     ((st + I < nst ? f(std::integral_constant<int, I>{}, st + I) : void()), ...);
 }
 
-template <int CW_, int NS_>
-__global__ __launch_bounds__(sh::NT, (160 * 1024) / (NS_ * sh::RS * CW_ * 2 + 4 * kShareMaxRun * sh::RG + 512))
+// RUN is the longest run a workgroup takes (LDS for its rows' list).
+template <int CW_, int NS_, int RUN>
+__global__ __launch_bounds__(sh::NT, (160 * 1024) / (NS_ * sh::RS * CW_ * 2 + 4 * RUN * sh::RG + 512))
 void share_product_kernel(ShareGroups G, int B) {
     using namespace sh;
     constexpr int ROWB = CW_ * 2;              // bytes per staged W row
@@ -272,7 +273,7 @@ void share_product_kernel(ShareGroups G, int B) {
     constexpr int DA = NS_ - 1;                // stages in flight ahead of the MFMAs
     constexpr int LPS = PER + RS / 16;         // vector loads per wave per stage (DMA + xs)
     static_assert(NB >= 1 && PER >= 1 && NS_ >= 3 && NS_ <= 8 && (DA - 1) * LPS < 64, "layout");
-    __shared__ int32_t rl[kShareMaxRun * RG];   // the run's union rows, each range padded to whole stages (-1)
+    __shared__ int32_t rl[RUN * RG];   // the run's union rows, each range padded to whole stages (-1)
     // one LDS object per ring slot: the compiler then sees that reading one
     // slot cannot alias the loads still landing in the others
     __shared__ __attribute__((aligned(1024))) char sl0[SLOT], sl1[SLOT], sl2[SLOT];
@@ -299,9 +300,9 @@ void share_product_kernel(ShareGroups G, int B) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the run's ranges r0 .. : range i's stages are [end[i-1], end[i])
     const int r0 = run * q.RM;
-    int end[kShareMaxRun], nst = 0;
+    int end[RUN], nst = 0;
 #pragma unroll
-    for (int i = 0; i < kShareMaxRun; ++i) {
+    for (int i = 0; i < RUN; ++i) {
         const bool on = i < q.RM && r0 + i < q.R;
         const int u = on ? min(max(q.cnt[r0 + i], 0), RG) : 0;      // written by the union kernel
         const int up = (u + RS - 1) / RS * RS;
@@ -348,7 +349,7 @@ void share_product_kernel(ShareGroups G, int B) {
         // stage st of the run is stage st - end[i-1] of its range i
         int row = st * RS;
 #pragma unroll
-        for (int i = 1; i < kShareMaxRun; ++i)
+        for (int i = 1; i < RUN; ++i)
             if (st >= end[i - 1]) row = i * 32 * RG + (st - end[i - 1]) * RS;
 #pragma unroll
         for (int ks = 0; ks < RS / 16; ++ks) {
@@ -493,13 +494,21 @@ hipError_t launch_share_products(ShareGroups G, int64_t B, hipStream_t stream) {
     int un = 0, pr = 0, rd = 0, blocks = 0;
     for (int i = 0; i < G.n; ++i) blocks += G.g[i].R * G.g[i].chunks;
     // Ranges per product workgroup: longer runs pay the prologue and the partials
-    // less often, as long as enough workgroups are left.  A step in us (8B layer,
-    // 1664 workgroups at one range each from eight sequences on) at 1 / 2 / 4: B = 16
-    // 134.7 / 127.6 / 123.1, B = 32 163 / 148 / 138; 1B layer (464) 53.5 / 50.6 / 53.2;
-    // 70B layer (6528) 444 / 391 / 367.  Narrow tiles, B = 4, r = 0.5: 8B (3328) 113 /
-    // 106 / 110, 1B (928) 46.5 / 43.6 / 45.8, 70B (13056) 369 / 329 / 313.
-    const int rm = share_cols(B) == 256 ? (blocks >= 800 ? 4 : blocks >= 400 ? 2 : 1)
-                                        : (blocks >= 6000 ? 4 : blocks >= 800 ? 2 : 1);
+    // less often, as long as enough workgroups are left.  Calls of one projection
+    // and of a layer's four at once (us at 1 / 2 / 4, r = 0.5; blocks = workgroups at
+    // one range each):
+    //   B >= 8: 8B gate|up (896) B = 16 60 / 56 / 55, B = 32 81 / 68 / 62; down (448) 43 / 41 /
+    //     44, 55 / 50 / 55; q|k|v (192) 29 / 32 / 41; 70B o (512) 45 / 42 / 45, gate|up (3584)
+    //     248 / 215 / 205; four of 1B (464) 43 / 40 / 43, 8B (1664) 125 / 117 / 113, 70B (6528)
+    //     427 / 375 / 352.  Runs of two of 513 to 799 blocks would put two workgroups on some
+    //     CUs only: 70B q|k|v (640) B = 32 64 / 66 / 56, 5120 -> 13824 (540) 72 / 72 / 60.
+    //   B < 8: 70B gate|up (7168) B = 4 199 / 179 / 169, down (3584) 105 / 97 / 97; 8B down (896)
+    //     39 / 39 / 37, q|k|v (384) 24 / 25 / 31; four of 1B (928) 33.5 / 33.4 / 35, 8B (3328)
+    //     101 / 96 / 99.  From 1024 to 2048 blocks runs of two leave just over one round of
+    //     workgroups, while three of the shorter ones fit a CU at once: 5120 -> 13824 (1080)
+    //     37.9 / 40.6 / 39.1, 8B gate|up (1792) 45.3 / 47.6 / 47.2, 70B q|k|v (1280) 43 / 44 / 50.
+    const int rm = share_cols(B) == 256 ? (blocks > 512 ? 4 : blocks >= 400 ? 2 : 1)
+                 : blocks >= 6000 ? 4 : blocks > 2048 || (blocks >= 800 && blocks <= 1024) ? 2 : 1;
     static_assert(kShareMaxRun == 4, "longest run");
     for (int i = 0; i < G.n; ++i) {
         ShareGroup &q = G.g[i];
@@ -517,12 +526,12 @@ hipError_t launch_share_products(ShareGroups G, int64_t B, hipStream_t stream) {
                        G, Bi);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (share_cols(B) == 256)
-        hipLaunchKernelGGL((share_product_kernel<256, 4>), dim3(static_cast<unsigned>(pr)), dim3(sh::NT), 0,
-                           stream, G, Bi);
-    else
-        hipLaunchKernelGGL((share_product_kernel<128, 6>), dim3(static_cast<unsigned>(pr)), dim3(sh::NT), 0,
-                           stream, G, Bi);
+    auto product = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(pr)), dim3(sh::NT), 0, stream, G, Bi);
+    };
+    if (share_cols(B) == 256) product(share_product_kernel<256, 4, kShareMaxRun>);
+    else if (rm == 1) product(share_product_kernel<128, 6, 1>);
+    else product(share_product_kernel<128, 6, kShareMaxRun>);
     if ((e = hipGetLastError()) != hipSuccess || rd == 0) return e;
     hipLaunchKernelGGL(share_reduce_kernel, dim3(static_cast<unsigned>(rd)), dim3(sh::NT), 0, stream, G, Bi);
     return hipGetLastError();

@@ -13,7 +13,10 @@ pytestmark = gpu
     (16, 2600, 17200, 1300),     # 408 workgroups at one range each: runs of two
     (8, 2600, 35000, 700),       # 822: runs of four, the last of two ranges
     (32, 512, 205000, 300),      # one range only: Y written directly
+    (9, 2600, 22000, 1300),      # 516: runs of four
     (3, 2600, 17200, 2600),      # narrow tiles: 810, runs of two, all rows kept
+    (5, 2600, 22000, 1000),      # ... 1032: one range each
+    (7, 2600, 44000, 500),       # ... 2064: runs of two
     (2, 2600, 128008, 200),      # ... 6006, runs of four
 ])
 def test_runs(B, K, N, k):
