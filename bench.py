@@ -20,6 +20,9 @@ K timed steps bracketed by device synchronisation.
 
   python bench.py [--gpus 1] [--steps 20] [--warmup 5] [--ratios 0.25,0.5,0.75,1.0]
 
+The line holds the headline, the roofline and, of every further record below,
+its rooflines and its entries at r = 0.5; --records FILE writes all of them.
+
 The same step is also timed under per-component retention ratios
 ("component_ratios": attention-side products, and optionally the MLP down
 projection, at 0.7 with the sensitive gate/up group dense), the policies the
@@ -150,6 +153,8 @@ def parse():
     p.add_argument("--workload", default="layer_8b")
     p.add_argument("--cpu-tokens", type=int, default=0,
                    help="tokens of the CPU-oracle sample (default: the whole layer)")
+    p.add_argument("--records", default=None, metavar="FILE",
+                   help="also write every record in full (all ratios, descriptions) to FILE as JSON")
     p.add_argument("--no-cpu-baseline", action="store_true")
     p.add_argument("--no-fused-attention", action="store_true",
                    help="skip the separate timing of the fused attention block")
@@ -1195,6 +1200,29 @@ def child_processes():
         return [f"unknown ({type(e).__name__})"]
 
 
+def summary(out):
+    """The printed line: of each further record its rooflines, its scalars and
+    its headline entries (the rest goes to --records).  The full record is
+    about 24 KB, longer than what a log keeps of its last line."""
+    step = ("ms_per_step", "tflops", "gemm_tflops", "speedup_vs_r1")
+    line = {}
+    for name, rec in out.items():
+        if name in ("sweep", "component_ratios"):
+            rows = rec if name == "sweep" else rec["policies"]
+            rec = {r: {k: v[k] for k in step} for r, v in rows.items()}
+        elif isinstance(rec, dict) and "op" in rec:
+            rec = {k: v for k, v in rec.items() if k not in ("op", "kernels")}
+            for table in ("per_ratio", "per_input_ratio", "per_batch_ratio", "per_length"):
+                if table not in rec:
+                    continue
+                rows = rec.pop(table)
+                h = str(HEADLINE_R)
+                keep = [k for k in rows if k == h or k.endswith("@" + h)] or list(rows)
+                rec[table] = {k: {c: x for c, x in rows[k].items() if "paper" not in c} for k in keep}
+        line[name] = rec
+    return line
+
+
 # ------------------------------------------------------------------ main
 
 def main():
@@ -1574,7 +1602,10 @@ def main():
         print(f"# CPU oracle on {tokens} tokens ...", file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline(wk, tokens, HEADLINE_R)
     out["children_at_exit"] = child_processes()
-    print(json.dumps(out), flush=True)
+    if args.records:
+        with open(args.records, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(summary(out)), flush=True)
 
 
 if __name__ == "__main__":
