@@ -1218,7 +1218,8 @@ def summary(out):
                 rows = rec.pop(table)
                 h = str(HEADLINE_R)
                 keep = [k for k in rows if k == h or k.endswith("@" + h)] or list(rows)
-                rec[table] = {k: {c: x for c, x in rows[k].items() if "paper" not in c} for k in keep}
+                rec[table] = {k: {c: x for c, x in rows[k].items() if "paper" not in c}
+                              if isinstance(rows[k], dict) else rows[k] for k in keep}
         line[name] = rec
     return line
 

@@ -57,6 +57,7 @@ def test_line_is_short_and_keeps_the_headline():
     out["norm_chain"] = {"op": "x" * 300, "per_input_ratio": {f"{i}@{r}": row for i in "ab" for r in ratios}}
     out["decode_batched"] = {"op": "x" * 300, "per_batch_ratio": {f"B{b}@{r}": row for b in (4, 16, 32) for r in ratios}}
     out["paper_kernels"] = {"op": "x" * 500, "per_length": dict.fromkeys(("1024", "2048", "4096"), row)}
+    out["layer_forward"] = {"op": "x" * 300, "per_ratio": {"rmm_ms@0.5": 2.0, "rmm_ms@1.0": 3.0, "dense_ms": 5.0}}
     out["component_ratios"] = {"op": "x" * 200, "policies": {"p": {**row, **times}}}
     line = bench.summary(out)
     assert len(json.dumps(line)) < 9000 < len(json.dumps(out))
@@ -67,4 +68,5 @@ def test_line_is_short_and_keeps_the_headline():
     assert list(line["decode_batched"]["per_batch_ratio"]) == ["B4@0.5", "B16@0.5", "B32@0.5"]
     assert list(line["paper_kernels"]["per_length"]) == ["1024", "2048", "4096"]
     assert line["component_ratios"] == {"p": times}
+    assert line["layer_forward"] == {"per_ratio": {"rmm_ms@0.5": 2.0}}
     assert out["decode"]["op"]                                # the record itself is left whole
