@@ -678,6 +678,7 @@ hipError_t launch_qk_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *
         const int64_t qb = (Lq + rowk::BQ - 1) / rowk::BQ, base = qb * batch * H;
         const bool lines = qk_lines(Lk, S), rows16 = qk_rows_ok(Lk, D, S);
         const bool square = 2 * Lq > Lk, half = causal && square;   // half: about half the tiles have a product
+        const bool shared = H > Hkv;                       // neighbouring blocks read the same keys
         // Long rows that share lines, once S is past the 256 MB that the memory side
         // cache absorbs: pieces shifted to lines, unless every other row starts at half
         // a line.  1 x 28 heads x 2712 keys, k = 64 121 [128-key tiles 159, gathered 154],
@@ -686,14 +687,16 @@ hipError_t launch_qk_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *
         const bool past = !lines && Lk >= 1408 && 2 * batch * H * Lq * Lk >= 320000000;
         const bool shift = past && (D == 64 || !(Lk % 32 == 0 && reinterpret_cast<uintptr_t>(S) % 64 == 0));
         // Gathered dims (half the matrix work at k = 64), with 256-key tiles, one block
-        // per CU: for the longest rows and the half-line ones above; causal from 4096 keys
+        // per CU: for the longest rows and the half-line ones above; causal from 3968 keys
         // on (1 x 32 heads x 4096, k = 32: 218 [237]); without the mask from 1280 keys on
         // if few dims are kept or rows share lines (1 x 64 x 4096, k = 32: 386 [436]; 1 x 8 x
-        // 3584 40 [43]; k = 64: 445 [447]).
+        // 3584 40 [43]; k = 64: 445 [447]).  Rows on lines whose heads share no keys: not,
+        // or later (32 / 32 heads x 4096, k = 64 248 [240], x 5504 437 [469]; 16 / 16 x 3072,
+        // k = 32, no mask 96 [74]).
         const bool gathered = D == 128 && k <= 64 && rows16 && !shift &&
             (qk_gathered(base, Lk, D, k, S) || past ||
-             (half ? (base >= 512 && Lk >= 4096) || (k <= 48 && base >= 1024 && Lk >= 1000 && Lk < 1280)
-                   : square && (k <= 48 || !lines) && ((base >= 512 && Lk >= 1280) || (base >= 160 && Lk >= 2000))));
+             (half ? (base >= 512 && Lk >= (shared || !lines ? 3968 : 4608)) || (k <= 48 && base >= 1024 && Lk >= 1000 && Lk < 1280)
+                   : square && (!lines || (shared && k <= 48)) && ((base >= 512 && Lk >= 1280) || (base >= 160 && Lk >= 2000))));
         // 256-key tiles (512-byte row pieces) otherwise for the longest rows (8192 keys,
         // k = 128: 802 [838]) and wherever S is past the cache off the lines
         const bool wide = D == 128 && (gathered || past || (lines && Lk >= 6144 && base >= 256));
@@ -706,9 +709,10 @@ hipError_t launch_qk_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *
         // 28 heads x 1000 keys, 224 blocks: 2 shares 15.6 [1: 20.0, 3: 19.0]; 4 x 32 x 384, 384
         // blocks: 1 share 13.2 [2: 17.8]), two rather than one where that costs little (1 x
         // 16 x 2240, 288 blocks: 42 [52]).  Long rows on lines: two (4096 keys, k = 128, no
-        // mask).
+        // mask; heads that share no keys from 1024 on, 64 / 64 x 1280 60 [73], 32 / 32 x 4096
+        // 227 [320]).
         const bool three = half && Lk >= 1280 && Lk < 3968 &&
-            (base > 512 || (base < 512 && base >= 171 && (tiles >= 20 || (D == 64 && tiles >= 11 && (base <= 200 || base >= 270)))));
+            (base > 512 || (base == 512 && !shared) || (base < 512 && base >= 171 && (base <= 200 || base >= 270) && tiles >= (D == 64 ? 11 : 20)));
         int64_t C = 1;
         if (wide || shift) {
             C = 1;
@@ -718,12 +722,13 @@ hipError_t launch_qk_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *
             C = (512 + base - 1) / base;
         } else if (base < 512) {
             int64_t least = tiles;
-            const bool two = base <= 352 || (tiles >= 18 && base <= 448);
+            const bool two = base <= 352 || !shared || (tiles >= 18 && base <= 448);
             for (int64_t c = 2; c <= (512 + base - 1) / base; ++c) {
                 const int64_t t = (base * c + 511) / 512 * ((tiles + c - 1) / c);
                 if (t < least || (c == 2 && two && t <= least + (tiles >= 9))) { least = t; C = c; }
             }
-        } else if (lines && base > 512 && Lk >= 2048 && (D == 128 || half || Lk < 4096)) {
+        } else if (lines && (shared ? base > 512 && Lk >= 2048 && (D == 128 || half || Lk < 4096)
+                                    : square && Lk >= 1024)) {
             C = 2;
         }
         if (C > tiles) C = tiles;
