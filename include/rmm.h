@@ -270,7 +270,7 @@ rmm_status_t rmm_reduced_gemv(const void *X, const void *W, const int32_t *idx,
  *   Y[b][m][n] = sum_{t < k} Xt[b][idx[b*k + t]][m] * W[idx[b*k + t]][n]
  *
  * Xt  : [B][K][ldxt] bf16, ldxt >= M.     W : [K][ldw] bf16, ldw >= N.
- * idx : int32 [B*k], ascending per unit, values in [0, K).
+ * idx : int32 [B*k], strictly ascending per unit, values in [0, K).
  * Y   : [B][M][ldy] bf16, ldy >= N, written.
  * Retained rows of Xt and W are read as 16-byte vectors and staged through
  * LDS; no compacted operand is written to memory.  bf16 only.
@@ -292,7 +292,7 @@ rmm_status_t rmm_reduced_gemm_kmajor(const void *Xt, const void *W, const int32_
  *   share a kv head), and S = -inf where causal != 0 and t > i + (Lk - Lq).
  *
  * Q     : [batch][H][Lq][D].   Kc : [batch][Hkv][Lk][D].
- * idx   : int32 [batch*H*k], ascending per head, values in [0, D) -- the
+ * idx   : int32 [batch*H*k], strictly ascending per head, values in [0, D) -- the
  *         per-head selection on Q (rmm_score + rmm_select with B = batch*H).
  * scale : multiplies the fp32 accumulator; the paper uses 1/sqrt(D) with
  *         the full head dimension.
@@ -341,7 +341,7 @@ rmm_status_t rmm_reduced_qk_rowstats(const void *Q, const void *Kc, const int32_
  *
  * Q   : [batch][H][Lq][D]    Kc, V : [batch][Hkv][Lk][D]    O : [batch][H][Lq][D]
  *       (contiguous; the value rows have the head dimension D).
- * idx : int32 [batch*H*k], each head's list ascending (from rmm_select).
+ * idx : int32 [batch*H*k], each head's list strictly ascending (from rmm_select).
  * workspace : rmm_workspace_size(RMM_OP_ATTENTION, batch*H, Lk, D, k) bytes,
  *       16-byte aligned; receives each query head's retained key dims as
  *       contiguous rows or, for few query rows against many keys, partial
@@ -381,7 +381,7 @@ rmm_status_t rmm_reduced_attention(const void *Q, const void *Kc, const void *V,
  * Wgu : bf16 [K][ldw], 2F columns in 128-column blocks: block 2q holds the
  *       gate weights of channels 128q .. 128q+127, block 2q+1 the up weights
  *       of the same channels (a column permutation of [Wg | Wu] made once at
- *       load time).  idx: int32 [B*k] ascending, as for rmm_reduced_gemm.
+ *       load time).  idx: int32 [B*k] strictly ascending, as for rmm_reduced_gemm.
  * Ht  : bf16 [B][F][ldht], ldht >= M, 16-byte aligned; columns M..ldht-1
  *       are not written.  energy: float64 [B][F], 8-byte aligned.
  * workspace : rmm_gemm_swiglu_workspace_size(B, M, F) bytes, 8-byte aligned
@@ -647,7 +647,7 @@ rmm_status_t rmm_decode_step(const rmm_decode_group_t *groups, int ngroups, int6
 
 /*
  * The reduced products of a decode step over caller-made sets, several at
- * once   (Sec. 3.2 reduced product; the boundary accepts any ascending list,
+ * once   (Sec. 3.2 reduced product; the boundary accepts any strictly ascending list,
  * e.g. sets computed for an earlier token or by another call).
  *
  * For each group g and sequence b: Y_g[b][n] = sum over t of
@@ -703,7 +703,7 @@ rmm_status_t rmm_decode_products_shared(const rmm_decode_group_t *groups, int ng
  * idx_g[b] = the TopK of X_g[b]^2 as rmm_decode_step selects it (the same
  * lists, bit for bit), then Y_g = rmm_decode_products_shared's products over
  * them -- one selection launch for all groups (plus one per group wider than
- * 32768 channels) and the four launches of the shared products.
+ * 32768 channels) and the three launches of the shared products.
  *
  * groups, B, workspace, errors: as rmm_decode_products_shared (the same
  * workspace size); idx_g is written.

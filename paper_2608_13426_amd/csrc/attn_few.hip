@@ -40,7 +40,10 @@ constexpr int TQ = 16;                     // query rows per workgroup
 constexpr int TS = 32;                     // keys per wave and stage
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kTau = 8.f;                // lazy-rescale threshold, log2 units
-constexpr int kBlocks = 512;               // workgroups aimed at (two per CU)
+// Workgroups aimed at: two per CU where four or eight heads share a workgroup.
+// One and two heads take 131 and 99 KB of LDS, so one workgroup per CU, and 512
+// of them are two rounds.
+constexpr int kBlocks = 512;
 constexpr int kMinTiles = 4;               // stages per split at least
 constexpr int kFewMaxRows = 256;           // query rows per head taken here at most
 

@@ -27,9 +27,9 @@
 //      in ascending order (a block scan), and the range's union rows and
 //      xs[b][row] (bf16, zeros past the union and for sequences that do not
 //      keep the row) go to the workspace;
-//   2. share_product_kernel, one workgroup per (run of 1, 2 or 4 ranges, column chunk: 128
-//      columns below eight sequences, 256 from eight on): the union rows of
-//      W stream through an LDS ring by LDS DMA (six slots of 32 rows, or
+//   2. share_product_kernel, one workgroup per (run of 1, 2 or 4 ranges,
+//      column chunk: 128 columns below eight sequences, 256 from eight on):
+//      the union rows of W stream through an LDS ring by LDS DMA (six slots of 32 rows, or
 //      four of the wider rows), W fragments come back with the
 //      transposing LDS read, xs fragments are loaded into registers with
 //      their stage; each run writes fp32 partials (or Y when there is one
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(sh::NT) void share_reduce_kernel(ShareGroups G, int
 size_t share_group_layout(int64_t B, int64_t N, int64_t K, void *ws, ShareGroup *q) {
     auto a256 = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
     const int64_t R = (K + kShareRange - 1) / kShareRange;
-    // unused; part of the size a caller has been asked for since the first version
+    // nothing is written there; part of the size that callers have been told
     const size_t head = a256(static_cast<size_t>(B * (R + 1)) * 4);
     const size_t rows = a256(static_cast<size_t>(R * kShareRange) * 4);
     const size_t cnt = a256(static_cast<size_t>(R) * 4);

@@ -75,8 +75,10 @@ hipError_t launch_gemm_kmajor_bf16(const uint16_t *Xt, const uint16_t *W, const 
 // the same product with per-unit weights: unit u reads W + (u / w_ugroup) *
 // w_ustride elements; with trim, Xt is known to be zero at (m, j) for
 // j > m + trim_off and each row tile stops its K loop there;
-// hipErrorNotSupported (nothing launched) when ldy >= 2^23 (the large-tile
-// kernel that implements these addresses Y rows with 32-bit offsets)
+// hipErrorNotSupported (nothing launched) when per-unit weights or trim meet
+// ldy >= 2^23: a limit of the entry points from when only the 256 x 256 tile
+// (32-bit offsets within a Y tile) had these forms.  The smaller tiles would
+// serve any ldy, but what was refused stays refused
 hipError_t launch_gemm_kmajor_grouped_bf16(const uint16_t *Xt, const uint16_t *W, const int32_t *idx,
                                           int64_t B, int64_t M, int64_t N, int64_t K, int64_t k,
                                           int64_t ldxt, int64_t ldw, uint16_t *Y, int64_t ldy,

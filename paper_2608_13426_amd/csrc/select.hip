@@ -15,7 +15,7 @@
 // fits.  Units of up to 256 keys (attention heads) skip the radix passes: every
 // thread ranks its own key against all of them.  For a unit of one token (a
 // decode step) the keys come straight from the token's activations: 16 (bf16)
-// or 31 (fp32) key bits, so at most two passes.
+// or 31 (fp32) key bits, so at most two passes for bf16 and four for fp32.
 //
 // What bounds it is the chain of dependent LDS passes and barriers of one
 // workgroup.
@@ -505,6 +505,9 @@ hipError_t launch_src(const void *src, int64_t ld, int64_t B, int64_t K, int64_t
     if (K <= 4096) return launch<1024, 4, true, SRC>(src, ld, B, K, k, 4, idx, stream);
     if (K <= 8192) return launch<1024, 8, true, SRC>(src, ld, B, K, k, 8, idx, stream);
     if (K <= 16384) return launch<1024, 16, true, SRC>(src, ld, B, K, k, 16, idx, stream);
+    // 32 keys of 64 bits per thread do not all fit its registers (some 500 bytes
+    // of scratch), and are still the faster form: 28672 energies 72 us before
+    // the ranked bucket, 56.5 with it
     if (K <= 32768) return launch<1024, 32, true, SRC>(src, ld, B, K, k, 32, idx, stream);
     const int cpt = static_cast<int>((K + 1023) / 1024);
     return launch<1024, 1, false, SRC>(src, ld, B, K, k, cpt, idx, stream);
