@@ -89,42 +89,42 @@ def _sources(main):
 # file, the shared headers and the build script) is the one it was measured
 # with, and for the same launch mix; re-run the counters after any change.
 GEMM_TRAFFIC = {"sources": _sources("gemm.hip"),
-                "sha256": "68ac2b7ad27c91221c97636ed8c27456ab2c122eefb3902319df8527e0e8c286",
+                "sha256": "a767defc5c73fda70753189b1ee59f3ca9697f0e550a790a2fa732793605d276",
                 "mix": "layer_8b r=0.25,0.5,0.75,1.0 grouped",
-                "bytes": round((399451.23 * 2.0 + 172205.58) * 1024)}
+                "bytes": round((399452.38 * 2.0 + 172150.92) * 1024)}
 # per fused attention call: attn_fwd_kernel (mean over the four ratios' kernels)
 # plus attn_compact_k_kernel
 ATTN_TRAFFIC = {"sources": _sources("attn.hip"),
-                "sha256": "75cb10788b12ed82b426504dd6f8518ef879e79f71f7bbd66d905d2950e631e6",
+                "sha256": "84ef893b0238578fac5e5038cc1ba925604f92562d391c774470ae6db82606b1",
                 "mix": "layer_8b r=0.25,0.5,0.75,1.0",
-                "bytes": round((103628.57 * 2.0 + 65550.01 + 8249.03 * 2.0 + 40960.00) * 1024)}
+                "bytes": round((103648.02 * 2.0 + 65553.05 + 8249.03 * 2.0 + 40960.00) * 1024)}
 # per rmm_rmsnorm_kmajor call (8192 x 4096, the same whatever r):
 # rms_block_kmajor_kernel and its score_finalize_grouped_kernel
 NORM_TRAFFIC = {"sources": _sources("norm.hip") + [os.path.join(CSRC, "score.hip")],
-                "sha256": "79fe0c69964059ec38392903ab8f2fb268e3151519f1ec51fc89194bfb724c5f",
+                "sha256": "d9a874ac704e6e00469b153040d18ad06862118972ea7df27f9961d4d9479351",
                 "mix": "layer_8b attn_in,mlp_in",
-                "bytes": round((33033.05 * 2.0 + 74192.68 + 4115.00 * 2.0 + 32.00) * 1024)}
+                "bytes": round((33033.05 * 2.0 + 74225.66 + 4115.00 * 2.0 + 32.00) * 1024)}
 
 # per rmm_decode_products call of the batch-1 decode step (the four 8B
 # groups; mean over the four ratios): gemv_partial_grouped_kernel and
 # gemv_reduce_grouped_kernel
 DECODE_TRAFFIC = {"sources": [os.path.join(CSRC, f) for f in ("gemv.hip", "kernels.h", "device_common.h")]
                   + [BUILD_SCRIPT],
-                  "sha256": "6b225f92ec31b39168f1a0be790ba59d66188460e2f01631e19cf5a94e2a2dbc",
+                  "sha256": "b5db95064e85969f192ded68c9b425c370d54edf8d3ad3fb13e66004862087ef",
                   "mix": "layer_8b r=0.25,0.5,0.75,1.0 B=1",
-                  "bytes": round(((53593.4 * 2.0 + 2661.2 + 1349.0 * 2.0 + 84.0)
-                                  + (106949.4 * 2.0 + 3430.0 + 1733.0 * 2.0 + 84.0)
-                                  + (160329.0 * 2.0 + 3947.9 + 1993.0 * 2.0 + 84.0)
-                                  + (213691.9 * 2.0 + 4223.7 + 2121.0 * 2.0 + 84.0)) / 4 * 1024)}
+                  "bytes": round(((53593.3 * 2.0 + 2660.8 + 1349.0 * 2.0 + 84.0)
+                                  + (106949.1 * 2.0 + 3431.4 + 1733.0 * 2.0 + 84.0)
+                                  + (160328.3 * 2.0 + 3948.0 + 1993.0 * 2.0 + 84.0)
+                                  + (213691.3 * 2.0 + 4222.4 + 2121.0 * 2.0 + 84.0)) / 4 * 1024)}
 # per rmm_decode_products_shared call at B = 16, r = 0.5 on the 8B groups:
 # its three kernels (union pass, product, reduction of the runs)
 SHARED_TRAFFIC = {"sources": [os.path.join(CSRC, f) for f in ("gemv_shared.hip", "gemv_shared.h",
                                                               "kernels.h", "device_common.h")]
                   + [BUILD_SCRIPT],
-                  "sha256": "c91a9a5074d75cbda43957970ce5194c26ef2cfa43cff701c36445623b487c3d",
+                  "sha256": "42b7088a6b560578e95ef482fa2894c2ecf8ea1f7c248d05e539fafaff2bc060",
                   "mix": "layer_8b B=16 r=0.5",
-                  "bytes": round((2748.3 * 2.0 + 937.5 + 217373.0 * 2.0 + 6656.9
-                                  + 3351.0 * 2.0 + 1344.0) * 1024)}
+                  "bytes": round((2748.3 * 2.0 + 937.6 + 217367.0 * 2.0 + 6657.0
+                                  + 3355.0 * 2.0 + 1344.0) * 1024)}
 
 
 def sources_sha256(paths):

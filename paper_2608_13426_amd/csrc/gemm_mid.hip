@@ -15,21 +15,22 @@
 //     to there.
 // Each output is one chain of MFMAs over the list in order, as in the other
 // bf16 kernels, so all of them give the same bits (four waves that split the
-// K loop of a 64 x 64 tile, added at the end, were no faster: 12.5 us against
-// 11.7 for the first shape below).
+// K loop of a 64 x 64 tile, added at the end, were no faster: 12.5 us for the
+// first shape below).
 // The retained list is read from LDS (segments of kMidSeg indices, copied by
 // the whole workgroup), because a staged row here is shorter than 512 bytes
 // and one load instruction covers 4 or 8 rows with a different index each.
 //
 // Measured against the register-staged 128 x 128 kernel these replace (us,
-// bf16): 37 x 4096 -> 6144 at r = 0.5 38.0 -> 11.7, 16 x 14336 -> 4096 at
-// r = 0.5 118 -> 32, 777 x 4096 -> 4096 at r = 0.8 63.8 -> 31.0 (670 TFLOP/s),
-// 2048 x 8192 -> 2048 at r = 0.5 77 -> 40 (855 TFLOP/s); and against the
-// 256 x 256 tile where that leaves half the chip idle, 2048 x 4096 -> 4096 at
-// r = 0.5 48.5 -> 39.5.  Also timed, no better: four waves of 64 x 64, 64-row
-// stages, three slots (31-48 us for the third shape); 256 x 128 and 128 x 256
-// tiles (43-48); 64 x 128 (42); for 64 x 64, 32- or 128-row stages (12.2-13.9
-// us for the first shape), tiles 32 wide (12.7-19).
+// bf16): 37 x 4096 -> 6144 at r = 0.5 38.0 -> 11.3, 16 x 14336 -> 4096 at
+// r = 0.5 118 -> 33, 777 x 4096 -> 4096 at r = 0.8 63.8 -> 32 to 34 (610 to
+// 650 TFLOP/s), 2048 x 8192 -> 2048 at r = 0.5 77 -> 40 (850 TFLOP/s); and
+// against the 256 x 256 tile where that leaves half the chip idle, 2048 x 4096
+// -> 4096 at r = 0.5 48.5 -> 37.4.  Also timed, no better (with a barrier that
+// did not yet wait for the LDS reads, 31.0 us for the third shape): four waves
+// of 64 x 64, 64-row stages, three slots (31-48 us for the third shape); 256 x
+// 128 and 128 x 256 tiles (43-48); 64 x 128 (42); for 64 x 64, 32- or 128-row
+// stages (12.2-13.9 us for the first shape), tiles 32 wide (12.7-19).
 #include <type_traits>
 
 #include "device_common.h"
