@@ -636,9 +636,10 @@ bool qk_rows_ok(int64_t Lk, int64_t D, const void *S) {
 namespace {
 // rows of S on 128-byte lines
 bool qk_lines(int64_t Lk, const void *S) { return Lk % 64 == 0 && reinterpret_cast<uintptr_t>(S) % 128 == 0; }
-// Gathered dims (half the matrix work) where the masked product no longer hides
-// behind the stores: 32 heads, k = 64, us masked / gathered: 8192 keys 841 / 792,
-// without the mask 850 / 813 (8 heads x 8192: 242 / 202).
+// Gathered dims (half the matrix work) where the masked product in 128-key tiles
+// no longer hides behind the stores: 32 heads, k = 64, us masked / gathered: 8192
+// keys 845 / 790 to 805, without the mask 850 / 813 (8 heads x 8192: 242 / 202).
+// Masked in 256-key tiles the first takes 771 to 790, within the runs' spread.
 bool qk_gathered(int64_t base, int64_t Lk, int64_t D, int64_t k, const void *S) {
     return D == 128 && k <= 64 && Lk >= 6144 && base >= 256 && qk_lines(Lk, S);
 }
@@ -698,7 +699,7 @@ hipError_t launch_qk_bf16(const uint16_t *Q, const uint16_t *Kc, const int32_t *
              (half ? (base >= 512 && Lk >= (shared || !lines ? 3968 : 4608)) || (k <= 48 && base >= 1024 && Lk >= 1000 && Lk < 1280)
                    : square && (!lines || (shared && k <= 48)) && ((base >= 512 && Lk >= 1280) || (base >= 160 && Lk >= 2000))));
         // 256-key tiles (512-byte row pieces) otherwise for the longest rows (8192 keys,
-        // k = 128: 802 [838]) and wherever S is past the cache off the lines
+        // k = 128: 760 to 788 [838]) and wherever S is past the cache off the lines
         const bool wide = D == 128 && (gathered || past || (lines && Lk >= 6144 && base >= 256));
         const int64_t tiles = (Lk + (wide ? 255 : 127)) / (wide ? 256 : 128);
         // Shares of the keys, two blocks of 128-key tiles per CU.  Causal rows of middle
