@@ -182,7 +182,7 @@ __global__ __launch_bounds__(NT) void select_rank_kernel(const void *__restrict_
 // contiguous run of the keys, its lanes every 64th of it (whole-line loads
 // and stores; positions come from ballots).  Unit u's keys start at element
 // u * ld of `src`.  Measured (random energies with 1 % outliers, k = K / 2):
-// 10.8 -> 7.2 us at K = 4096 and 24.9 -> 16.4 at K = 14336, against radix
+// 10.8 -> 7.0 us at K = 4096 and 24.9 -> 15.2 at K = 14336, against radix
 // passes down to the last digit over keys owned in runs per thread.
 constexpr int kRankMax = 128;      // ranked at once: two per lane (256: 9.6 us instead of 6.4 at K = 1024)
 template <int NT, int C, bool REG, int SRC>
@@ -226,6 +226,16 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
         else return load_key<SRC>(e, c0 + static_cast<int64_t>(kWave) * c);
     };
     const int n_own = static_cast<int>(max<int64_t>(0, min<int64_t>(chunk, (K - c0 + kWave - 1) / kWave)));
+    // f over the lane's keys; unrolled where they are held (indexed at run time they
+    // would live in scratch)
+    auto each = [&](auto &&f) {
+        if constexpr (REG) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) f(c);
+        } else {
+            for (int c = 0; c < chunk; ++c) f(c);
+        }
+    };
 
     // The leading bits shared by every key need no pass (energies of one
     // unit usually share sign and most of the exponent): take the workgroup's
@@ -234,11 +244,12 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
     // the keys over its buckets.
     constexpr int SH = SRC == kEnergy ? 32 : 0;
     uint32_t kmin = ~0u, kmax = 0;
-    for (int c = 0; c < n_own; ++c) {
+    each([&](int c) {
+        if (c >= n_own) return;
         const uint32_t u = static_cast<uint32_t>(key_at(c) >> SH);
         kmin = min(kmin, u);
         kmax = max(kmax, u);
-    }
+    });
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
         kmin = min(kmin, static_cast<uint32_t>(__shfl_xor(static_cast<int>(kmin), o, kWave)));
@@ -286,14 +297,15 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
         if (n == need) { tie = K; decided = true; break; }      // the whole bucket is kept
         if (n <= kRankMax) {
             // rank the bucket's keys: the one with need - 1 before it is the k-th
-            for (int c = 0; c < n_own; ++c) {
+            each([&](int c) {
+                if (c >= n_own) return;
                 const uint64_t u = key_at(c);
                 if ((u & mask) == prefix) {
                     const uint32_t p = atomicAdd(&s_n, 1u);
                     cand_key[p] = u;
                     cand_idx[p] = static_cast<int32_t>(c0 + kWave * c);
                 }
-            }
+            });
             __syncthreads();
             uint64_t ck[kRankMax / kWave];
             int32_t ci[kRankMax / kWave];
@@ -326,16 +338,17 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
         // `need` of them by index
         auto tied = [&](int c) { return c < n_own && (key_at(c) & mask) == prefix; };
         uint32_t n_cand = 0;
-        for (int c = 0; c < chunk; ++c)
+        each([&](int c) {
             n_cand += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(tied(c))));
+        });
         uint32_t cand = waves_before<NT>(n_cand, scan_buf);
-        for (int c = 0; c < chunk; ++c) {
+        each([&](int c) {
             const bool t = tied(c);
             const uint64_t m = __builtin_amdgcn_ballot_w64(t);
             if (t && cand + static_cast<uint32_t>(__builtin_popcountll(m & below)) == need - 1)
                 s_tie = static_cast<int32_t>(c0 + static_cast<int64_t>(kWave) * c);
             cand += static_cast<uint32_t>(__builtin_popcountll(m));
-        }
+        });
         __syncthreads();
         tie = s_tie;
     }
@@ -344,14 +357,6 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
         if (c >= n_own) return false;
         const uint64_t p = key_at(c) & mask;
         return p > prefix || (p == prefix && c0 + static_cast<int64_t>(kWave) * c <= tie);
-    };
-    auto each = [&](auto &&f) {
-        if constexpr (REG) {
-#pragma unroll
-            for (int c = 0; c < C; ++c) f(c);
-        } else {
-            for (int c = 0; c < chunk; ++c) f(c);
-        }
     };
     uint32_t n_sel = 0;
     each([&](int c) {
@@ -505,10 +510,17 @@ hipError_t launch_src(const void *src, int64_t ld, int64_t B, int64_t K, int64_t
     if (K <= 4096) return launch<1024, 4, true, SRC>(src, ld, B, K, k, 4, idx, stream);
     if (K <= 8192) return launch<1024, 8, true, SRC>(src, ld, B, K, k, 8, idx, stream);
     if (K <= 16384) return launch<1024, 16, true, SRC>(src, ld, B, K, k, 16, idx, stream);
-    // 32 keys of 64 bits per thread do not all fit its registers (some 500 bytes
-    // of scratch), and are still the faster form: 28672 energies 72 us before
-    // the ranked bucket, 56.5 with it
-    if (K <= 32768) return launch<1024, 32, true, SRC>(src, ld, B, K, k, 32, idx, stream);
+    // 32 keys of 64 bits per thread do not all fit its registers (340 bytes of
+    // scratch); reading the keys again is faster (us, energies, re-read / held: 1 x
+    // 16801 32 / 43, 64 x 16801 33 / 55, 1024 x 16801 155 / 299, 1 x 28672 48 / 47, 512 x
+    // 28672 119 / 169; fp32 tokens 256 x 28672 59 / 64) unless they are energies past
+    // what the L2s hold and in one round of workgroups (256 x 28672 98 / 71, 128 x
+    // 24000 75 / 65; 257 x 28672 98 / 122).  Held and indexed at run time, all of
+    // the keys lay in scratch: 50, 66, 373, 57, 192; 73; 79, 71, 138.
+    if constexpr (SRC == kEnergy) {
+        if (K <= 32768 && B <= 256 && B * K >= 3000000)
+            return launch<1024, 32, true, SRC>(src, ld, B, K, k, 32, idx, stream);
+    }
     const int cpt = static_cast<int>((K + 1023) / 1024);
     return launch<1024, 1, false, SRC>(src, ld, B, K, k, cpt, idx, stream);
 }

@@ -48,3 +48,36 @@ def test_select_edges(kind, B, K):
         got = idx.cpu().numpy().reshape(B, k)
         for b in range(B):
             assert np.array_equal(got[b], _top(e[b], k)), (kind, B, K, k, b)
+
+
+# more than 16384 keys: read again, or held in registers (energies, up to 256 units
+# of 3e6 keys and more together)
+@pytest.mark.parametrize("kind", ["bulk", "ties", "special"])
+@pytest.mark.parametrize("B,K", [(1, 32768), (2, 32769), (91, 32768), (92, 32768), (146, 20480), (183, 16400)])
+def test_select_wide_units(kind, B, K):
+    dev = require_gpu()
+    rng = np.random.default_rng(B + K)
+    e = _values(kind, rng, B, K)
+    for k in (K // 3, K):
+        idx = torch.full((B * k,), -1, dtype=torch.int32, device=dev)
+        rmm.rmm_select(torch.from_numpy(e).to(dev), k, idx)
+        got = idx.cpu().numpy().reshape(B, k)
+        for b in range(0, B, max(1, B // 12)):
+            assert np.array_equal(got[b], _top(e[b], k)), (kind, B, K, k, b)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,K", [(1, 16385), (3, 32768), (2, 33000)])
+def test_select_wide_tokens(dtype, B, K):
+    dev = require_gpu()
+    g = torch.Generator().manual_seed(K)
+    X = torch.randn(B, K + 1, generator=g).to(dtype)
+    X[:, ::97] *= 20
+    X = X.to(dev)[:, 1:] if dtype == torch.bfloat16 else X.to(dev)[:, :K]     # bf16 off 16-byte boundaries
+    e = X.cpu().double().numpy() ** 2
+    for k in (1, K // 2):
+        idx = torch.full((B * k,), -1, dtype=torch.int32, device=dev)
+        rmm.rmm_select_tokens(X, k, idx)
+        got = idx.cpu().numpy().reshape(B, k)
+        for b in range(B):
+            assert np.array_equal(got[b], _top(e[b], k)), (dtype, B, K, k, b)
