@@ -226,14 +226,23 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
         else return load_key<SRC>(e, c0 + static_cast<int64_t>(kWave) * c);
     };
     const int n_own = static_cast<int>(max<int64_t>(0, min<int64_t>(chunk, (K - c0 + kWave - 1) / kWave)));
-    // f over the lane's keys; unrolled where they are held (indexed at run time they
-    // would live in scratch)
+    // f over the lane's places (each) or the keys it has (own); unrolled where they
+    // are held (indexed at run time they would live in scratch)
     auto each = [&](auto &&f) {
         if constexpr (REG) {
 #pragma unroll
             for (int c = 0; c < C; ++c) f(c);
         } else {
             for (int c = 0; c < chunk; ++c) f(c);
+        }
+    };
+    auto own = [&](auto &&f) {
+        if constexpr (REG) {
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (c < n_own) f(c);
+        } else {
+            for (int c = 0; c < n_own; ++c) f(c);
         }
     };
 
@@ -244,8 +253,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
     // the keys over its buckets.
     constexpr int SH = SRC == kEnergy ? 32 : 0;
     uint32_t kmin = ~0u, kmax = 0;
-    each([&](int c) {
-        if (c >= n_own) return;
+    own([&](int c) {
         const uint32_t u = static_cast<uint32_t>(key_at(c) >> SH);
         kmin = min(kmin, u);
         kmax = max(kmax, u);
@@ -277,17 +285,10 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
         // digit: bits top .. shift (up to 8 of them)
         const int shift = max(0, top - 7);
         const uint64_t dmask = (1ull << (top - shift + 1)) - 1;
-        if constexpr (REG) {
-#pragma unroll
-            for (int c = 0; c < C; ++c)
-                if (c < n_own && (keys[c] & mask) == prefix)
-                    atomicAdd(&hmine[(keys[c] >> shift) & dmask], 1u);
-        } else {
-            for (int c = 0; c < n_own; ++c) {
-                const uint64_t u = key_at(c);
-                if ((u & mask) == prefix) atomicAdd(&hmine[(u >> shift) & dmask], 1u);
-            }
-        }
+        own([&](int c) {
+            const uint64_t u = key_at(c);
+            if ((u & mask) == prefix) atomicAdd(&hmine[(u >> shift) & dmask], 1u);
+        });
         pick_digit(hcopy, need, wtot, s_pick);
         need -= s_pick[1];
         prefix |= static_cast<uint64_t>(s_pick[0]) << shift;
@@ -297,8 +298,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
         if (n == need) { tie = K; decided = true; break; }      // the whole bucket is kept
         if (n <= kRankMax) {
             // rank the bucket's keys: the one with need - 1 before it is the k-th
-            each([&](int c) {
-                if (c >= n_own) return;
+            own([&](int c) {
                 const uint64_t u = key_at(c);
                 if ((u & mask) == prefix) {
                     const uint32_t p = atomicAdd(&s_n, 1u);
