@@ -8,7 +8,7 @@
 // the k-th largest, using LDS histograms with integer atomics
 // (order-independent counts).  It starts below the leading bits every key
 // shares and stops as soon as that bucket is taken whole or holds at most
-// kRankMax keys; those are then ranked directly (a wave per key: ballots over
+// kRankMax (kRankShort) keys; those are then ranked directly (a wave per key: ballots over
 // the others).  Keys tied with the k-th key are taken lowest index first, and
 // the kept indices are compacted in ascending order with one workgroup prefix
 // scan.  Each thread owns a contiguous chunk of keys, kept in registers when it
@@ -185,6 +185,10 @@ __global__ __launch_bounds__(NT) void select_rank_kernel(const void *__restrict_
 // 10.8 -> 7.0 us at K = 4096 and 24.9 -> 15.2 at K = 14336, against radix
 // passes down to the last digit over keys owned in runs per thread.
 constexpr int kRankMax = 128;      // ranked at once: two per lane (256: 9.6 us instead of 6.4 at K = 1024)
+// Of up to 1024 keys a radix pass costs less than ranking more than a few (us for
+// 257 keys with a limit of 128 / 24: 256 units 7.4 / 6.1, 4096 units 32.3 / 26.2;
+// from 800 keys on limits of 16 to 128 differ by less than 2 %).
+constexpr int kRankShort = 32;
 template <int NT, int C, bool REG, int SRC>
 __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src, int64_t ld,
                                                     int64_t K, int64_t k, int cpt,
@@ -296,7 +300,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const void *__restrict__ src
         top = shift - 1;
         const uint32_t n = s_pick[2];
         if (n == need) { tie = K; decided = true; break; }      // the whole bucket is kept
-        if (n <= kRankMax) {
+        if (n <= (REG && NT * C <= 1024 ? kRankShort : kRankMax)) {
             // rank the bucket's keys: the one with need - 1 before it is the k-th
             own([&](int c) {
                 const uint64_t u = key_at(c);
@@ -504,10 +508,18 @@ hipError_t launch_src(const void *src, int64_t ld, int64_t B, int64_t K, int64_t
                            static_cast<int>(K), static_cast<int>(k), idx);
         return hipGetLastError();
     }
+    // Half as many threads with twice the keys where several units share a CU and the
+    // fixed work of a workgroup adds up (us at half / all threads: 768 x 512 8.2 / 8.7,
+    // 4096 x 512 22.6 / 28.0, 2048 x 800 15.1 / 18.0, 320 x 8192 19.1 / 22.7, 2048 x 8192
+    // 73.5 / 96.0; 256 x 512 6.7 / 6.3, 512 x 800 8.3 / 8.1, 256 x 8192 16.2 / 13.9).
+    const bool half = B > 256;
+    if (K <= 512 && half) return launch<256, 2, true, SRC>(src, ld, B, K, k, 2, idx, stream);
     if (K <= 512) return launch<512, 1, true, SRC>(src, ld, B, K, k, 1, idx, stream);
+    if (K <= 1024 && B >= 1024) return launch<256, 4, true, SRC>(src, ld, B, K, k, 4, idx, stream);
     if (K <= 1024) return launch<512, 2, true, SRC>(src, ld, B, K, k, 2, idx, stream);
     if (K <= 2048) return launch<512, 4, true, SRC>(src, ld, B, K, k, 4, idx, stream);
     if (K <= 4096) return launch<1024, 4, true, SRC>(src, ld, B, K, k, 4, idx, stream);
+    if (K <= 8192 && half) return launch<512, 16, true, SRC>(src, ld, B, K, k, 16, idx, stream);
     if (K <= 8192) return launch<1024, 8, true, SRC>(src, ld, B, K, k, 8, idx, stream);
     if (K <= 16384) return launch<1024, 16, true, SRC>(src, ld, B, K, k, 16, idx, stream);
     // 32 keys of 64 bits per thread do not all fit its registers (340 bytes of

@@ -50,6 +50,23 @@ def test_select_edges(kind, B, K):
             assert np.array_equal(got[b], _top(e[b], k)), (kind, B, K, k, b)
 
 
+# more units than CUs: half as many threads per unit up to 512 and from 4097 to 8192 keys, and
+# from 1024 units on up to 1024 keys
+@pytest.mark.parametrize("kind", ["bulk", "ties", "zeros", "close", "special"])
+@pytest.mark.parametrize("B,K", [(256, 257), (257, 257), (300, 512), (256, 4097), (257, 4097), (260, 8192),
+                                 (1023, 513), (1024, 513), (1030, 1024)])
+def test_select_many_units(kind, B, K):
+    dev = require_gpu()
+    rng = np.random.default_rng(B + K)
+    e = _values(kind, rng, B, K)
+    for k in (1, K // 2, K):
+        idx = torch.full((B * k,), -1, dtype=torch.int32, device=dev)
+        rmm.rmm_select(torch.from_numpy(e).to(dev), k, idx)
+        got = idx.cpu().numpy().reshape(B, k)
+        for b in range(0, B, max(1, B // 12)):
+            assert np.array_equal(got[b], _top(e[b], k)), (kind, B, K, k, b)
+
+
 # more than 16384 keys: read again, or held in registers (energies, up to 256 units
 # of 3e6 keys and more together)
 @pytest.mark.parametrize("kind", ["bulk", "ties", "special"])
