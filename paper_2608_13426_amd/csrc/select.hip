@@ -8,11 +8,11 @@
 // the k-th largest, using LDS histograms with integer atomics
 // (order-independent counts).  It starts below the leading bits every key
 // shares and stops as soon as that bucket is taken whole or holds at most
-// kRankMax (kRankShort) keys; those are then ranked directly (a wave per key: ballots over
-// the others).  Keys tied with the k-th key are taken lowest index first, and
+// kRankMax keys (kRankShort in short units); those are then ranked directly (a
+// wave per key: ballots over the others).  Keys tied with the k-th key are taken lowest index first, and
 // the kept indices are compacted in ascending order with one workgroup prefix
 // scan.  Each thread owns a contiguous chunk of keys, kept in registers when it
-// fits.  Units of up to 256 keys (attention heads) skip the radix passes: every
+// fits.  Units of up to 128 keys (attention heads) skip the radix passes: every
 // thread ranks its own key against all of them.  For a unit of one token (a
 // decode step) the keys come straight from the token's activations: 16 (bf16)
 // or 31 (fp32) key bits, so at most two passes for bf16 and four for fp32.
@@ -137,8 +137,8 @@ __device__ __forceinline__ uint64_t load_key(const void *row, int64_t j) {
 
 // Units of K <= NT / 4 keys: the quad of lanes t ranks key t against all of
 // them (each lane a quarter; ties to the lower index) and keeps it if fewer
-// than k come before it.  128 heads x 128 keys: 3.6 us against 7.0 for
-// the radix passes.
+// than k come before it.  128 keys, us against the radix passes: 32 units 4.8 /
+// 5.8, 1024 units 6.2 / 8.2.
 template <int NT, int SRC>
 __global__ __launch_bounds__(NT) void select_rank_kernel(const void *__restrict__ src, int64_t ld, int K,
                                                          int k, int32_t *__restrict__ idx) {
@@ -502,12 +502,14 @@ hipError_t launch(const void *src, int64_t ld, int64_t B, int64_t K, int64_t k, 
 template <int SRC>
 hipError_t launch_src(const void *src, int64_t ld, int64_t B, int64_t K, int64_t k, int32_t *idx,
                       hipStream_t stream) {
-    if (K <= 256) {
-        auto rank = K <= 128 ? select_rank_kernel<512, SRC> : select_rank_kernel<1024, SRC>;
-        hipLaunchKernelGGL(rank, dim3(static_cast<unsigned>(B)), dim3(K <= 128 ? 512 : 1024), 0, stream, src, ld,
-                           static_cast<int>(K), static_cast<int>(k), idx);
+    if (K <= 128) {
+        hipLaunchKernelGGL((select_rank_kernel<512, SRC>), dim3(static_cast<unsigned>(B)), dim3(512), 0, stream, src,
+                           ld, static_cast<int>(K), static_cast<int>(k), idx);
         return hipGetLastError();
     }
+    // one key per thread (us, radix / every key ranked by 1024 threads: 1 x 160 4.7 / 5.7,
+    // 512 x 160 6.7 / 8.9, 4096 x 256 20.5 / 44.9)
+    if (K <= 256) return launch<256, 1, true, SRC>(src, ld, B, K, k, 1, idx, stream);
     // Half as many threads with twice the keys where several units share a CU and the
     // fixed work of a workgroup adds up (us at half / all threads: 768 x 512 8.2 / 8.7,
     // 4096 x 512 22.6 / 28.0, 2048 x 800 15.1 / 18.0, 320 x 8192 19.1 / 22.7, 2048 x 8192
@@ -588,7 +590,8 @@ hipError_t launch_select_tokens_grouped(const GemvGroups &G, int64_t B, hipStrea
 
 hipError_t launch_select_tokens(const void *X, bool bf16, int64_t B, int64_t K, int64_t ldx,
                                 int64_t k, int32_t *idx, hipStream_t stream) {
-    // up to 256 channels (a decode step's heads) every key is ranked directly
+    // up to 256 channels (a decode step's heads) the generic selection: every key
+    // ranked directly, or one key per thread
     if (K > 256 && bf16 && K <= kToken16MaxK && reinterpret_cast<uintptr_t>(X) % 16 == 0 && ldx % 8 == 0) {
         if (K <= 8 * 256) return launch_token16<256, 8>(X, ldx, B, K, k, idx, stream);
         if (K <= 16 * 256) return launch_token16<256, 16>(X, ldx, B, K, k, idx, stream);

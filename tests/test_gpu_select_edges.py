@@ -50,10 +50,11 @@ def test_select_edges(kind, B, K):
             assert np.array_equal(got[b], _top(e[b], k)), (kind, B, K, k, b)
 
 
-# more units than CUs: half as many threads per unit up to 512 and from 4097 to 8192 keys, and
-# from 1024 units on up to 1024 keys
+# one key per thread from 129 to 256 keys; more units than CUs: half as many threads per
+# unit up to 512 and from 4097 to 8192 keys, and from 1024 units on up to 1024 keys
 @pytest.mark.parametrize("kind", ["bulk", "ties", "zeros", "close", "special"])
-@pytest.mark.parametrize("B,K", [(256, 257), (257, 257), (300, 512), (256, 4097), (257, 4097), (260, 8192),
+@pytest.mark.parametrize("B,K", [(2, 129), (300, 129), (40, 255), (1030, 256), (256, 257), (257, 257),
+                                 (300, 512), (256, 4097), (257, 4097), (260, 8192),
                                  (1023, 513), (1024, 513), (1030, 1024)])
 def test_select_many_units(kind, B, K):
     dev = require_gpu()
