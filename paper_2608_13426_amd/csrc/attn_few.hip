@@ -342,29 +342,53 @@ __global__ __launch_bounds__(256) void attn_few_merge_kernel(const float *__rest
     reinterpret_cast<uint32_t *>(O)[row * (fewk::D / 2) + lane] = pack_bf16x2(v[0], v[1]);
 }
 
-// Ot[bh*D + d][q] and its energies for 16 dims of one head (blockIdx.x): a
-// thread merges one dim of a row at a time, up to 32 rows at once, through LDS into
-// rows of Ot; the energies are added over the queries in a fixed order (Lq % 8 ==
-// 0, Lq <= 256, rows of Ot 16-byte aligned).  32 heads on 8 kv heads x 4000 keys,
-// the whole call in us, 8 / 64 / 256 rows: 17 / 28 / 59 (a thread per dim walking all
-// rows 38 / 163 / 293, the prefill kernel 93 / 94 / 95).
-constexpr int kKmRows = 32, kKmDims = 16;
-__global__ __launch_bounds__(kKmRows *kKmDims) void attn_few_merge_kmajor_kernel(
+// Ot[bh*D + d][q] and its energies, the queries in order: a thread per dim of one
+// head walks the rows, without LDS or barriers (the same conditions as below)
+__global__ __launch_bounds__(fewk::D) void attn_few_merge_dims_kernel(
     const float *__restrict__ part, uint16_t *__restrict__ Ot, int64_t ldot, double *__restrict__ energy, int Lq,
     int S, int64_t rows) {
-    constexpr int LR = fewk::kFewMaxRows + 8;                  // staged dim row (16-byte aligned)
-    __shared__ __attribute__((aligned(16))) uint16_t val[kKmDims][LR];
-    __shared__ double en[kKmDims][fewk::kFewMaxRows / 8];
-    const int tid = threadIdx.x, nt = blockDim.x, d0 = kKmDims * static_cast<int>(blockIdx.x);
+    const int64_t bh = blockIdx.x, row_t = bh * fewk::D + threadIdx.x;
+    double e = 0.0;
+    for (int q0 = 0; q0 < Lq; q0 += 8) {
+        uint32_t w[4];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            float v[1];
+            merge_row(part, rows, bh * Lq + q0 + q, S, static_cast<int>(threadIdx.x), v);
+            const uint32_t x = f32_to_bf16(v[0]);
+            const double y = static_cast<double>(__uint_as_float(x << 16));
+            e = fma(y, y, e);
+            w[q >> 1] = q & 1 ? w[q >> 1] | (x << 16) : x;
+        }
+        *reinterpret_cast<uint4 *>(Ot + row_t * ldot + q0) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    energy[row_t] = e;
+}
+
+// Ot[bh*D + d][q] and its energies for DIMS dims of one head (blockIdx.x): a
+// thread merges one dim of a row at a time, up to ROWS rows at once, through LDS into
+// rows of Ot; the energies are added over the queries in a fixed order (Lq % 8 ==
+// 0, Lq <= MAXR, rows of Ot 16-byte aligned).  32 heads on 8 kv heads x 4000 keys,
+// the whole call in us with 16 dims, 8 / 64 / 256 rows: 17 / 28 / 59 (a thread per dim
+// walking all rows 38 / 163 / 293, the prefill kernel 93 / 94 / 95).  Many heads need
+// no such split, and fewer, larger workgroups take less (the rule below).
+template <int DIMS, int ROWS, int MAXR>
+__global__ __launch_bounds__(ROWS *DIMS) void attn_few_merge_kmajor_kernel(
+    const float *__restrict__ part, uint16_t *__restrict__ Ot, int64_t ldot, double *__restrict__ energy, int Lq,
+    int S, int64_t rows) {
+    constexpr int LR = MAXR + 8;                               // staged dim row (16-byte aligned)
+    __shared__ __attribute__((aligned(16))) uint16_t val[DIMS][LR];
+    __shared__ double en[DIMS][MAXR / 8];
+    const int tid = threadIdx.x, nt = blockDim.x, d0 = DIMS * static_cast<int>(blockIdx.x);
     const int64_t bh = blockIdx.y;
-    for (int q = tid / kKmDims; q < Lq; q += nt / kKmDims) {
+    for (int q = tid / DIMS; q < Lq; q += nt / DIMS) {
         float v[1];
-        merge_row(part, rows, bh * Lq + q, S, d0 + tid % kKmDims, v);
-        val[tid % kKmDims][q] = f32_to_bf16(v[0]);
+        merge_row(part, rows, bh * Lq + q, S, d0 + tid % DIMS, v);
+        val[tid % DIMS][q] = f32_to_bf16(v[0]);
     }
     __syncthreads();
     const int nq = Lq / 8;
-    for (int i = tid; i < kKmDims * nq; i += nt) {
+    for (int i = tid; i < DIMS * nq; i += nt) {
         const int d = i / nq, c = i % nq;
         const uint4 x = *reinterpret_cast<const uint4 *>(&val[d][8 * c]);
         *reinterpret_cast<uint4 *>(Ot + (bh * fewk::D + d0 + d) * ldot + 8 * c) = x;
@@ -380,7 +404,7 @@ __global__ __launch_bounds__(kKmRows *kKmDims) void attn_few_merge_kmajor_kernel
         en[d][c] = e;
     }
     __syncthreads();
-    if (tid < kKmDims) {
+    if (tid < DIMS) {
         double e = 0.0;
         for (int c = 0; c < nq; ++c) e += en[tid][c];
         energy[bh * fewk::D + d0 + tid] = e;
@@ -471,8 +495,18 @@ hipError_t launch_attn_few_kmajor_bf16(const uint16_t *Q, const uint16_t *Kc, co
     float *part = static_cast<float *>(workspace);
     const hipError_t e = launch_splits(Q, Kc, V, idx, batch, H, Hkv, Lq, Lk, k, scale, causal, nullptr, part, &S, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_few_merge_kmajor_kernel, dim3(fewk::D / kKmDims, static_cast<unsigned>(batch * H)),
-                       dim3(kKmDims * static_cast<unsigned>(Lq < kKmRows ? Lq : kKmRows)), 0, stream, part, Ot, ldot, energy, static_cast<int>(Lq), S, batch * H * Lq);
+    auto merge = [&](auto kern, int dims, int at_once) {
+        hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(fewk::D / dims), static_cast<unsigned>(batch * H)),
+                           dim3(static_cast<unsigned>(dims * (Lq < at_once ? Lq : at_once))), 0, stream, part, Ot,
+                           ldot, energy, static_cast<int>(Lq), S, batch * H * Lq);
+    };
+    // us, 16 dims / 128 dims / a thread per dim: 512 heads x 8 rows x 64 keys 12.0 / 10.7 /
+    // 12.1, 1024 x 8 x 1000 36.6 / 33.5 / 36.1, 1792 x 8 x 64 22.7 / 17.7 / 17.2, 8192 x 8 x 64
+    // 67.5 / 51.9 / 45.5, 4096 x 24 x 300 113 / 94.7 / 95.9; 256 x 16 x 300 15.5 / 16.8 / 22.9
+    if (Lq > 32 || batch * H < 512) merge(attn_few_merge_kmajor_kernel<16, 32, fewk::kFewMaxRows>, 16, 32);
+    else if (batch * H < 1536 || Lq > 16) merge(attn_few_merge_kmajor_kernel<128, 4, 32>, 128, 4);
+    else hipLaunchKernelGGL(attn_few_merge_dims_kernel, dim3(static_cast<unsigned>(batch * H)), dim3(fewk::D), 0,
+                            stream, part, Ot, ldot, energy, static_cast<int>(Lq), S, batch * H * Lq);
     return hipGetLastError();
 }
 

@@ -64,7 +64,10 @@ def test_few_rows(b, H, Hkv, Lq, Lk, r, causal, scale):
 
 
 @pytest.mark.parametrize("b,H,Hkv,Lq,Lk", [(2, 8, 2, 8, 600), (1, 4, 4, 16, 150), (1, 2, 1, 8, 40),
-                                           (1, 4, 1, 256, 1300), (1, 4, 2, 248, 1100), (1, 2, 2, 200, 900)])
+                                           (1, 4, 1, 256, 1300), (1, 4, 2, 248, 1100), (1, 2, 2, 200, 900),
+                                           # many heads: the merge's other forms
+                                           (64, 8, 2, 8, 120), (64, 8, 4, 32, 300), (96, 16, 4, 24, 250),
+                                           (192, 8, 2, 8, 70), (96, 16, 4, 16, 200)])
 def test_few_rows_kmajor_same_bits(b, H, Hkv, Lq, Lk):
     """The K-major form holds the plain block's values bit for bit, with their energies."""
     dev = require_gpu()
