@@ -1105,10 +1105,14 @@ hipError_t launch_gemm_f32(const float *X, const float *W, const int32_t *idx, i
     (void)K;
     const bool vec = reinterpret_cast<uintptr_t>(W) % 16 == 0 && ldw % 4 == 0;
     const bool vec_y = reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 4 == 0;
-    // 64 x 64 tiles once they give every CU one, 32 x 32 (a quarter of the work
-    // per workgroup) below
+    // 64 x 64 tiles once they give every CU one and no half of them would be empty,
+    // 32 x 32 (a quarter of the work per workgroup) below.  Lists of up to 16 and 32
+    // indices in tiles of that many (us, BK 16 / 32 / 64: 256 x 4 x 18 -> 611, k = 14 10.2 /
+    // 13.2 / 19.6; 256 x 94 x 9 -> 2426, k = 7 71 / 93).  Up to 32 rows or columns, 32 x 32 / 64 x 64 tiles: 256 x 13 x 83
+    // -> 1170, k = 42 35 / 41; 64 x 16 x 1024 -> 1024, k = 512 45 / 64; 1 x 16 x 4096 -> 16384,
+    // k = 2048 51 / 87.
     const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64) * B;
-    const int t = t64 >= 256 ? 64 : 32;
+    const int t = t64 >= 256 && M > 32 && N > 32 ? 64 : 32;
     auto launch = [&](auto kernel) {
         dim3 grid(static_cast<unsigned>((N + t - 1) / t), static_cast<unsigned>((M + t - 1) / t),
                   static_cast<unsigned>(B));
@@ -1116,15 +1120,18 @@ hipError_t launch_gemm_f32(const float *X, const float *W, const int32_t *idx, i
                            static_cast<int>(N), static_cast<int>(k), ldx, ldw, ldy);
         return hipGetLastError();
     };
-    if (t == 64)
-        return vec ? (vec_y ? launch(gemm_gather_f32_kernel<64, 64, 32, true, true>)
-                            : launch(gemm_gather_f32_kernel<64, 64, 32, true, false>))
-                   : (vec_y ? launch(gemm_gather_f32_kernel<64, 64, 32, false, true>)
-                            : launch(gemm_gather_f32_kernel<64, 64, 32, false, false>));
-    return vec ? (vec_y ? launch(gemm_gather_f32_kernel<32, 32, 64, true, true>)
-                        : launch(gemm_gather_f32_kernel<32, 32, 64, true, false>))
-               : (vec_y ? launch(gemm_gather_f32_kernel<32, 32, 64, false, true>)
-                        : launch(gemm_gather_f32_kernel<32, 32, 64, false, false>));
+    auto pick = [&](auto bm, auto bk) {
+        constexpr int BM = decltype(bm)::value, BK = decltype(bk)::value;
+        return vec ? (vec_y ? launch(gemm_gather_f32_kernel<BM, BM, BK, true, true>)
+                            : launch(gemm_gather_f32_kernel<BM, BM, BK, true, false>))
+                   : (vec_y ? launch(gemm_gather_f32_kernel<BM, BM, BK, false, true>)
+                            : launch(gemm_gather_f32_kernel<BM, BM, BK, false, false>));
+    };
+    using I16 = std::integral_constant<int, 16>;
+    using I32 = std::integral_constant<int, 32>;
+    using I64 = std::integral_constant<int, 64>;
+    if (t == 64) return k <= 16 ? pick(I64{}, I16{}) : pick(I64{}, I32{});
+    return k <= 16 ? pick(I32{}, I16{}) : k <= 32 ? pick(I32{}, I32{}) : pick(I32{}, I64{});
 }
 
 }  // namespace rmm

@@ -108,6 +108,13 @@ def test_pv_kmajor_causal_trim(H, Hkv, Lq, Lk, kt):
     (1, 1025, 96, 1030, 31, 2),     # 64 x 64 tiles: list shorter than a tile, 8-byte rows
     (3, 600, 100, 640, 97, 0),      # ... several units
     (1, 1025, 96, 1029, 31, 3),     # ... 16-byte rows of Y, cut by N
+    (2, 17, 20, 50, 16, 2),         # 32 x 32, lists of one tile of 16
+    (2, 17, 20, 50, 17, 2),         # ... one index past it
+    (64, 32, 40, 130, 33, 0),       # 32 x 32 though 64 x 64 would fill the chip: half empty
+    (64, 33, 40, 130, 33, 0),       # ... 64 x 64 one row later
+    (64, 33, 40, 130, 15, 1),       # 64 x 64, lists below 16
+    (2, 17, 40, 50, 32, 2),         # 32 x 32, lists of one tile of 32
+    (128, 100, 40, 20, 17, 0),      # 32 x 32: few columns
 ])
 def test_f32_tiles(B, M, K, N, k, wpad):
     dev = require_gpu()
