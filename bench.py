@@ -89,9 +89,9 @@ def _sources(main):
 # file, the shared headers and the build script) is the one it was measured
 # with, and for the same launch mix; re-run the counters after any change.
 GEMM_TRAFFIC = {"sources": _sources("gemm.hip"),
-                "sha256": "a767defc5c73fda70753189b1ee59f3ca9697f0e550a790a2fa732793605d276",
+                "sha256": "510c5fd7b3df9f6aa45504e2d1a8c9a97dd5e4171651fe12105d13834ecd666b",
                 "mix": "layer_8b r=0.25,0.5,0.75,1.0 grouped",
-                "bytes": round((399452.38 * 2.0 + 172150.92) * 1024)}
+                "bytes": round((399448.59 * 2.0 + 172156.71) * 1024)}
 # per fused attention call: attn_fwd_kernel (mean over the four ratios' kernels)
 # plus attn_compact_k_kernel
 ATTN_TRAFFIC = {"sources": _sources("attn.hip"),
